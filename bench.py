@@ -338,9 +338,11 @@ def history_fold_bytes(g, s):
 
 
 def group_channels(g, tw, j):
-    """Channels of tile group j (T groups of contiguous tiles) of a block-deferred group."""
+    """Channels of tile group j (at most T groups of contiguous tiles) of a block-deferred
+    group."""
     n_tiles = -(-g["n"] // tw)
-    tpg = -(-n_tiles // block_of(g))
+    # at most one tile group per push of a block, of at least 98304 channels
+    tpg = max(-(-n_tiles // block_of(g)), min(n_tiles, -(-98304 // tw)))
     t0, t1 = j * tpg, min((j + 1) * tpg, n_tiles)
     if t0 >= t1:
         return 0

@@ -486,10 +486,9 @@ __device__ __forceinline__ void deferred_pass(const DeferredArgs &a)
         if (tile >= g.n_tiles) return;
     } else {
         // Flush of tile group j, block q: scheduled at push T q + j
-        // (fixed_group -1; the counter is advanced after this push), requested
-        // for one tile group (fixed_group >= 0) or for every tile group
-        // (fixed_group -2: the grid spans all tiles).  Skipped when that block
-        // is already folded.
+        // (fixed_group -1; the counter is advanced after this push), or
+        // requested for every tile group (fixed_group -2: the grid spans all
+        // tiles).  Skipped when that block is already folded.
         int j;
         int64_t q;
         if (a.fixed_group == -2) {
@@ -498,14 +497,9 @@ __device__ __forceinline__ void deferred_pass(const DeferredArgs &a)
             if (tile >= g.n_tiles) return;
             j = (int)(tile / a.tiles_per_group);
         } else {
-            if (a.fixed_group >= 0) {
-                j = a.fixed_group;
-                q = a.fixed_block;
-            } else {
-                const int64_t S = *a.step + 1;
-                j = (int)(S % T);
-                q = S / T;
-            }
+            const int64_t S = *a.step + 1;
+            j = (int)(S % T);
+            q = S / T;
             tile = (int64_t)j * a.tiles_per_group + slot;
             if (tile >= g.n_tiles || slot >= a.tiles_per_group) return;
         }
@@ -603,24 +597,6 @@ __global__ void colsum_final_kernel(const double *groups, int64_t n_groups, int 
     double s = 0.0;
     for (int64_t q = 0; q < n_groups; ++q) s += groups[(size_t)q * ne + e];
     out[e] = s;
-}
-
-// Record that tile group j folded block q (runs after the flush kernel).
-__global__ void flush_commit_kernel(DeferredArgs a)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int T = a.g.defer_t;
-    int j;
-    int64_t q;
-    if (a.fixed_group >= 0) {
-        j = a.fixed_group;
-        q = a.fixed_block;
-    } else {
-        const int64_t S = *a.step + 1;
-        j = (int)(S % T);
-        q = S / T;
-    }
-    if (q >= 1 && a.flushed[j] < q) a.flushed[j] = q;
 }
 
 template <int K, int P, int T, int NT, bool READ, bool HIST>
@@ -765,19 +741,6 @@ hipError_t launch_flush_fold(const DeferredArgs &a, hipStream_t st)
 hipError_t launch_history_fold(const DeferredArgs &a, hipStream_t st)
 {
     return launch_deferred_t<false, true>(a, st);
-}
-
-hipError_t launch_flush_commit(const DeferredArgs &a, hipStream_t st)
-{
-    hipLaunchKernelGGL(flush_commit_kernel, dim3(1), dim3(64), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_flush(const DeferredArgs &a, hipStream_t st)
-{
-    hipError_t e = launch_flush_fold(a, st);
-    if (e != hipSuccess) return e;
-    return launch_flush_commit(a, st);
 }
 
 int64_t deferred_readout_rows(const GroupArgs &g) { return g.n_tiles * (int64_t)g.tw / 64; }

@@ -63,11 +63,20 @@ constexpr int kDeferT = 256;
 constexpr int kDeferTMin = 128;
 // Pushes per block of the block-deferred one-level window (corr_window.hip).
 constexpr int kWindowT = 64;
-// Tile groups of a block-deferred group: T of them; tile group j folds block
-// q (pushes (T (q-1), T q]) at push T q + j, so every push flushes one group;
-// the level-0 ring keeps 2 T + p slots.  Arrays of tile groups hold
+// Tile groups of a block-deferred group: at most T of them; tile group j folds
+// block q (pushes (T (q-1), T q]) at push T q + j, so a push flushes at most
+// one group; the level-0 ring keeps 2 T + p slots.  Arrays of tile groups hold
 // kFlushGroups (the largest T) entries.
 constexpr int kFlushGroups = kDeferT;
+// A tile group holds at least this many channels (or the whole channel group),
+// so that a fold has enough waves to stream its state: a fold is a chain of
+// 256 dependent rows and takes 24 us however few channels it has, against 60
+// us for 98304 (1536 waves; 5.2 TB/s).  Of 250047 channels a pass of 512 pushes
+// and a readout took 14.9 ms with a fold of 1024 channels on every push, 5.4
+// with 16384, 5.2 with 49152 and 5.1 with 98304 and 196608; of 3e6 channels 256
+// pushes and a readout 8.8, 8.6, 8.2, 7.3 and 7.3 ms.  Beyond 256 x 98304
+// channels every push folds one group in any case.
+constexpr int64_t kFoldMinChannels = 98304;
 // Threads per block of the fold kernels (the scheduled flush takes 64, 128 or
 // 256; a tile wider than a block is split over several blocks).
 constexpr int kFoldThreadsDefault = 128;
@@ -131,9 +140,9 @@ struct DeferredArgs {
                             // the increment of its push, a readout after it)
     int64_t *flushed;       // [kFlushGroups] last block folded per tile group
     int64_t tiles_per_group;
-    int32_t fixed_group;    // >= 0: fold block fixed_block of this tile group; -2: of
-                            // every tile group that has not folded it; -1: the
-                            // flush scheduled for the push being issued
+    int32_t fixed_group;    // -2: fold block fixed_block of every tile group that has
+                            // not folded it; -1: the flush scheduled for the push
+                            // being issued
     int32_t ne;             // readout: number of (level, lag) entries
     int64_t fixed_block;
     int64_t ch_begin, ch_end;       // readout: channels reduced

@@ -30,12 +30,10 @@ int rhok_mfma_chunks(int n_mtiles, int nw); // blocks along the M tiles (grid.x)
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st);
 bool deferred_supported(int kind, int p, int m);
 hipError_t launch_stage(const GroupArgs &g, const int64_t *step, hipStream_t st);
-hipError_t launch_flush(const DeferredArgs &a, hipStream_t st);        // fold + commit
 hipError_t launch_flush_fold(const DeferredArgs &a, hipStream_t st);   // the fold kernel
 // Fold of block a.fixed_block for every tile group (a.fixed_group == -2) with
 // level 0 read from the history a.hist (a.hist_stride bytes per push).
 hipError_t launch_history_fold(const DeferredArgs &a, hipStream_t st);
-hipError_t launch_flush_commit(const DeferredArgs &a, hipStream_t st); // flag update
 int64_t deferred_readout_rows(const GroupArgs &g);
 int64_t deferred_readout_groups(const GroupArgs &g);
 int64_t deferred_readout_group_rows(); // chunk rows per fixed-order column group

@@ -518,15 +518,17 @@ __global__ void push_end_kernel(PushEndArgs a)
             __syncthreads();
         }
     }
+    if (a.commit_block >= 1) {
+        // every tile group folded block commit_block
+        for (int i = 0; i < a.n_flushed; ++i)
+            for (int j = threadIdx.x; j < a.defer_t[i]; j += blockDim.x)
+                if (a.flushed[i][j] < a.commit_block) a.flushed[i][j] = a.commit_block;
+    }
     if (threadIdx.x != 0) return;
     const int64_t S = *a.step + 1;
     for (int i = 0; i < a.n_flushed; ++i) {
         const int T = a.defer_t[i];
-        if (a.commit_block >= 1) {
-            // every tile group folded block commit_block
-            for (int j = 0; j < T; ++j)
-                if (a.flushed[i][j] < a.commit_block) a.flushed[i][j] = a.commit_block;
-        } else {
+        if (a.commit_block < 1) {
             const int j = (int)(S % T);
             const int64_t q = S / T;
             if (q >= 1 && a.flushed[i][j] < q) a.flushed[i][j] = q;
