@@ -479,7 +479,7 @@ __device__ __forceinline__ void deferred_pass(const DeferredArgs &a)
         // Readout (all tile groups caught up): fold the pushes after the
         // last complete block without writing state, for the tiles that hold
         // the pass's chunk rows [row_begin, row_end).
-        const int64_t S = *a.step;
+        const int64_t S = pushes_before(a.step);
         f = (S / T) * T;
         r = (int)(S - f);
         tile = (a.row_begin * 64) / g.tw + slot;
@@ -487,23 +487,25 @@ __device__ __forceinline__ void deferred_pass(const DeferredArgs &a)
     } else {
         // Flush of tile group j, block q: scheduled at push T q + j
         // (fixed_group -1; the counter is advanced after this push), or
-        // requested for every tile group (fixed_group -2: the grid spans all
-        // tiles).  Skipped when that block is already folded.
+        // requested for the tile groups of [tile_first, tile_end) (fixed_group
+        // -2).  Skipped when that block is already folded (a captured push,
+        // replayed after a readout; elsewhere the host knows and asks for no
+        // such fold).
         int j;
         int64_t q;
         if (a.fixed_group == -2) {
             q = a.fixed_block;
-            tile = slot;
-            if (tile >= g.n_tiles) return;
+            tile = a.tile_first + slot;
+            if (tile >= a.tile_end) return;
             j = (int)(tile / a.tiles_per_group);
         } else {
-            const int64_t S = *a.step + 1;
+            const int64_t S = pushes_before(a.step) + 1;
             j = (int)(S % T);
             q = S / T;
             tile = (int64_t)j * a.tiles_per_group + slot;
             if (tile >= g.n_tiles || slot >= a.tiles_per_group) return;
         }
-        if (q < 1 || a.flushed[j] >= q) return;
+        if (q < 1 || (a.flushed && a.flushed[j] >= q)) return;
         f = (q - 1) * T;
         r = T;
     }
@@ -607,7 +609,7 @@ hipError_t launch_deferred_kpt(const DeferredArgs &a, hipStream_t st)
     // readout: the tiles that hold chunk rows [row_begin, row_end); every
     // tile group: all tiles; otherwise the tiles of one tile group
     const int64_t read_tiles = (a.row_end * 64 + a.g.tw - 1) / a.g.tw - (a.row_begin * 64) / a.g.tw;
-    const int64_t tiles = READ ? read_tiles : a.fixed_group == -2 ? a.g.n_tiles : a.tiles_per_group;
+    const int64_t tiles = READ ? read_tiles : a.fixed_group == -2 ? a.tile_end - a.tile_first : a.tiles_per_group;
     const int64_t grid = tiles * parts;
     if (grid < 1) return hipSuccess;
     if constexpr (READ)
@@ -672,9 +674,9 @@ constexpr int kStageUnroll = 4;
 // (the large step 0.244 against 0.253 ms).
 typedef float stage_f4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, const int64_t *step, int aligned)
+__global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, int aligned)
 {
-    const int64_t s = *step + 1;
+    const int64_t s = pushes_before(step) + 1;
     const int slot = (int)((s - 1) % g.p0);
     const float *src = static_cast<const float *>(g.samples);
     const int64_t n = g.n_ch;
@@ -716,7 +718,7 @@ __global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, const int64_t *
 
 } // namespace
 
-hipError_t launch_stage(const GroupArgs &g, const int64_t *step, hipStream_t st)
+hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st)
 {
     // single-precision samples only (the deferred form's kinds); 16-byte
     // vectors need a 16-byte aligned source

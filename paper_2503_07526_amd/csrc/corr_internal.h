@@ -34,6 +34,14 @@ enum Kind : int32_t {
     K_COUNT = 8
 };
 
+// Pushes completed before the one being issued: the host's count, passed by
+// value, or a device counter that a captured graph's kernels read at every
+// replay.
+struct StepRef {
+    const int64_t *counter; // device counter, or null: `count`
+    int64_t count;
+};
+
 struct GroupArgs {
     const void *samples; // this push's samples (device), n_ch elements
     char *state;         // tile 0 of the group
@@ -110,6 +118,10 @@ struct FoldStamps {
 } // namespace corr
 #include <hip/hip_runtime.h>
 namespace corr {
+__device__ __forceinline__ int64_t pushes_before(const StepRef &r)
+{
+    return r.counter ? *r.counter : r.count;
+}
 __device__ __forceinline__ bool stamp_sampled(const FoldStamps *st)
 {
     return *st->step % st->stride == 0;
@@ -136,15 +148,16 @@ __device__ __forceinline__ void stamp_end(FoldStamps *st, unsigned block)
 // Flush / readout of a block-deferred group.
 struct DeferredArgs {
     GroupArgs g;
-    const int64_t *step;    // device push counter (a scheduled flush runs before
-                            // the increment of its push, a readout after it)
-    int64_t *flushed;       // [kFlushGroups] last block folded per tile group
+    StepRef step;           // flush: pushes before the one being issued; readout: all
+    int64_t *flushed;       // [kFlushGroups] last block folded per tile group, or null
+                            // where the host's record of it decides
     int64_t tiles_per_group;
-    int32_t fixed_group;    // -2: fold block fixed_block of every tile group that has
-                            // not folded it; -1: the flush scheduled for the push
-                            // being issued
+    int32_t fixed_group;    // -2: fold block fixed_block of the tile groups of tiles
+                            // [tile_first, tile_end); -1: the flush scheduled for the
+                            // push being issued
     int32_t ne;             // readout: number of (level, lag) entries
     int64_t fixed_block;
+    int64_t tile_first, tile_end;   // fixed_group -2
     int64_t ch_begin, ch_end;       // readout: channels reduced
     int64_t slice_begin, slice_end; // readout: channels written to slice_out
     int64_t row_begin, row_end;     // readout: the 64-channel chunk rows of this pass
@@ -166,7 +179,7 @@ struct PushArgs {
     int32_t n_groups;
     int32_t pad_;
     int64_t total_tiles;
-    const int64_t *step; // device: pushes completed before this one
+    StepRef step;        // pushes completed before this one
 };
 
 // Number of accumulator planes of a kind (2 for compensated sums).

@@ -10,11 +10,11 @@ namespace corr {
 
 hipError_t launch_push_batched(const PushArgs &a, int cpt, int lch, int grid, int block,
                                hipStream_t st);
-hipError_t launch_push_group(const GroupArgs &g, const int64_t *step, int cpt, int lch, int block,
+hipError_t launch_push_group(const GroupArgs &g, StepRef step, int cpt, int lch, int block,
                              hipStream_t st);
-hipError_t launch_push_window(const GroupArgs &g, const int64_t *step, int cpt, int lch,
+hipError_t launch_push_window(const GroupArgs &g, StepRef step, int cpt, int lch,
                               int block, int lags_per_block, hipStream_t st);
-hipError_t launch_push_split(const GroupArgs &g, const int64_t *step, int cpt, int lch, int block,
+hipError_t launch_push_split(const GroupArgs &g, StepRef step, int cpt, int lch, int block,
                              int lags_per_block, hipStream_t st);
 hipError_t launch_push_end(const PushEndArgs &a, hipStream_t st); // flush records + step counter
 hipError_t launch_rhok(const RhokArgs &a, hipStream_t st);
@@ -29,7 +29,7 @@ hipError_t rhok_mfma_prepare(int table_rows, int nw, int nmax); // once per cont
 int rhok_mfma_chunks(int n_mtiles, int nw); // blocks along the M tiles (grid.x)
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st);
 bool deferred_supported(int kind, int p, int m);
-hipError_t launch_stage(const GroupArgs &g, const int64_t *step, hipStream_t st);
+hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st);
 hipError_t launch_flush_fold(const DeferredArgs &a, hipStream_t st);   // the fold kernel
 // Fold of block a.fixed_block for every tile group (a.fixed_group == -2) with
 // level 0 read from the history a.hist (a.hist_stride bytes per push).
@@ -47,12 +47,12 @@ hipError_t launch_deferred_readout_final(const DeferredArgs &a, const double *gr
 hipError_t launch_gather(const ReduceArgs &a, hipStream_t st);
 bool window_deferred_supported(int kind);
 int window_lags_per_block(int p);
-hipError_t launch_window_fold(const GroupArgs &g, const int64_t *step, hipStream_t st);
+hipError_t launch_window_fold(const GroupArgs &g, StepRef step, hipStream_t st);
 // Two block-deferred windows of the same kind and length in one launch (the
 // second's blocks after the first's): a small window alone keeps few waves
 // per SIMD.
 bool window_folds_share_launch(const GroupArgs &a, const GroupArgs &b);
-hipError_t launch_window_fold2(const GroupArgs &a, const GroupArgs &b, const int64_t *step, hipStream_t st);
+hipError_t launch_window_fold2(const GroupArgs &a, const GroupArgs &b, StepRef step, hipStream_t st);
 
 } // namespace corr
 

@@ -392,7 +392,7 @@ __device__ __forceinline__ void dispatch_tile(const GroupArgs &g, int64_t tile, 
 template <int CPT, int LCH>
 __global__ __launch_bounds__(256) void push_batched_kernel(PushArgs a)
 {
-    const int64_t s = *a.step + 1;
+    const int64_t s = pushes_before(a.step) + 1;
 #pragma unroll 1
     for (int64_t t = blockIdx.x; t < a.total_tiles; t += gridDim.x) {
         int gi = 0;
@@ -417,9 +417,9 @@ __global__ __launch_bounds__(256) void push_batched_kernel(PushArgs a)
 // Plain form: one group per launch, one block per tile, kind fixed at compile
 // time (NTA: accumulator rows streamed, for groups larger than the cache).
 template <int K, int CPT, int LCH, bool PAIR, bool NTA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void push_group_kernel(GroupArgs g, const int64_t *step)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void push_group_kernel(GroupArgs g, StepRef step)
 {
-    const int64_t s = *step + 1;
+    const int64_t s = pushes_before(step) + 1;
     push_tile<K, CPT, LCH, PAIR, NTA>(g, (int64_t)blockIdx.x, s);
 }
 
@@ -427,9 +427,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void p
 // (lags_per_block each), so that more than one block per tile works on it;
 // block y = 0 also writes the ring slots and runs the cascade.
 template <int K, int CPT, int LCH>
-__global__ __launch_bounds__(256) void push_split_kernel(GroupArgs g, const int64_t *step, int lags_per_block)
+__global__ __launch_bounds__(256) void push_split_kernel(GroupArgs g, StepRef step, int lags_per_block)
 {
-    const int64_t s = *step + 1;
+    const int64_t s = pushes_before(step) + 1;
     const int lo = (int)blockIdx.y * lags_per_block;
     push_tile<K, CPT, LCH>(g, (int64_t)blockIdx.x, s, lo, lo + lags_per_block, blockIdx.y == 0);
 }
@@ -440,11 +440,11 @@ __global__ __launch_bounds__(256) void push_split_kernel(GroupArgs g, const int6
 // (slot - L) mod p, never the slot this push writes (that would be lag p), so
 // the chunks are independent; chunk 0 writes the new sample.
 template <int K, int CPT, int LCH, bool PAIR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void push_window_kernel(GroupArgs g, const int64_t *step, int lags_per_block)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void push_window_kernel(GroupArgs g, StepRef step, int lags_per_block)
 {
     using S = typename KT<K>::S;
     using A = typename KT<K>::A;
-    const int64_t s = *step + 1;
+    const int64_t s = pushes_before(step) + 1;
     const int64_t tile = blockIdx.x;
     const int tw = g.tw, p = g.p;
     const int lane_off = (int)threadIdx.x * CPT;
@@ -559,7 +559,7 @@ hipError_t launch_push_batched(const PushArgs &a, int cpt, int lch, int grid, in
 }
 
 template <int CPT, int LCH, bool PAIR, bool NTA>
-static hipError_t launch_group_t(const GroupArgs &g, const int64_t *step, int block,
+static hipError_t launch_group_t(const GroupArgs &g, StepRef step, int block,
                                  hipStream_t st)
 {
     const dim3 grid((unsigned)g.n_tiles);
@@ -577,7 +577,7 @@ static hipError_t launch_group_t(const GroupArgs &g, const int64_t *step, int bl
 }
 
 template <bool PAIR, bool NTA>
-static hipError_t launch_push_group_p(const GroupArgs &g, const int64_t *step, int cpt, int lch,
+static hipError_t launch_push_group_p(const GroupArgs &g, StepRef step, int cpt, int lch,
                                       int block, hipStream_t st)
 {
     if (cpt == 1 && lch == 16) return launch_group_t<1, 16, PAIR, NTA>(g, step, block, st);
@@ -589,7 +589,7 @@ static hipError_t launch_push_group_p(const GroupArgs &g, const int64_t *step, i
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_push_group(const GroupArgs &g, const int64_t *step, int cpt, int lch, int block,
+hipError_t launch_push_group(const GroupArgs &g, StepRef step, int cpt, int lch, int block,
                              hipStream_t st)
 {
     // pair groups keep cached accumulators (one form each)
@@ -599,7 +599,7 @@ hipError_t launch_push_group(const GroupArgs &g, const int64_t *step, int cpt, i
 }
 
 template <int CPT, int LCH, bool PAIR>
-static hipError_t launch_window_t(const GroupArgs &g, const int64_t *step, int block,
+static hipError_t launch_window_t(const GroupArgs &g, StepRef step, int block,
                                   int lags_per_block, hipStream_t st)
 {
     const dim3 grid((unsigned)g.n_tiles, (unsigned)((g.p + lags_per_block - 1) / lags_per_block));
@@ -617,7 +617,7 @@ static hipError_t launch_window_t(const GroupArgs &g, const int64_t *step, int b
 }
 
 template <bool PAIR>
-static hipError_t launch_push_window_p(const GroupArgs &g, const int64_t *step, int cpt, int lch,
+static hipError_t launch_push_window_p(const GroupArgs &g, StepRef step, int cpt, int lch,
                                        int block, int lags_per_block, hipStream_t st)
 {
     if (cpt == 1 && lch == 16) return launch_window_t<1, 16, PAIR>(g, step, block, lags_per_block, st);
@@ -630,7 +630,7 @@ static hipError_t launch_push_window_p(const GroupArgs &g, const int64_t *step, 
 }
 
 template <int CPT, int LCH>
-static hipError_t launch_split_t(const GroupArgs &g, const int64_t *step, int block,
+static hipError_t launch_split_t(const GroupArgs &g, StepRef step, int block,
                                  int lags_per_block, hipStream_t st)
 {
     const dim3 grid((unsigned)g.n_tiles, (unsigned)((g.p + lags_per_block - 1) / lags_per_block));
@@ -647,7 +647,7 @@ static hipError_t launch_split_t(const GroupArgs &g, const int64_t *step, int bl
     return hipGetLastError();
 }
 
-hipError_t launch_push_split(const GroupArgs &g, const int64_t *step, int cpt, int lch, int block,
+hipError_t launch_push_split(const GroupArgs &g, StepRef step, int cpt, int lch, int block,
                              int lags_per_block, hipStream_t st)
 {
     if (lags_per_block < 1 || g.pair || g.deferred) return hipErrorInvalidValue;
@@ -661,7 +661,7 @@ hipError_t launch_push_split(const GroupArgs &g, const int64_t *step, int cpt, i
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_push_window(const GroupArgs &g, const int64_t *step, int cpt, int lch,
+hipError_t launch_push_window(const GroupArgs &g, StepRef step, int cpt, int lch,
                               int block, int lags_per_block, hipStream_t st)
 {
     if (lags_per_block < 1 || g.levels != 1) return hipErrorInvalidValue;

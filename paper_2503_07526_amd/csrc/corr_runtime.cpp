@@ -112,6 +112,12 @@ struct corr_ctx {
     // at its end
     int64_t *d_step = nullptr;
     int64_t *d_step_side = nullptr;
+    // The device counters and flush records are kept only where a captured
+    // graph or the device stamps read them (counted); elsewhere the host's
+    // count and records go to the kernels by value and a push needs no end
+    // kernel (4 us of a push on the stream, a third launch of a
+    // block-deferred push and the second of a per-step one).
+    bool counted = false;
     int64_t n_push = 0;
     int32_t defer_t = 0;       // pushes per fold block of the block-deferred groups
     int32_t fold_threads = kFoldThreadsDefault;
@@ -391,13 +397,17 @@ int next_events(corr_ctx *c, int which, hipEvent_t *a, hipEvent_t *b)
     return CORR_OK;
 }
 
+StepRef step_main(const corr_ctx *c) { return c->counted ? StepRef{c->d_step, 0} : StepRef{nullptr, c->n_push}; }
+// (the sets that run on the side stream)
+StepRef step_side(const corr_ctx *c) { return c->counted ? StepRef{c->d_step_side, 0} : StepRef{nullptr, c->n_push}; }
+
 DeferredArgs deferred_args(const corr_ctx *c, int i)
 {
     const Group &g = c->groups[(size_t)i];
     DeferredArgs da{};
     da.g = c->pargs.g[(size_t)i];
-    da.step = c->d_step;
-    da.flushed = g.d_flushed;
+    da.step = step_main(c);
+    da.flushed = c->counted ? g.d_flushed : nullptr;
     da.tiles_per_group = g.tiles_per_group;
     da.fixed_group = -1;
     da.threads = c->fold_threads;
@@ -412,13 +422,14 @@ int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1)
 {
     if (f0) HIP_TRY(c, hipEventRecord(f0, st));
     for (int i : c->deferred_set) {
-        // no launch for a tile group without tiles, or before the first block
-        // is complete (a captured push keeps its launch, which then exits at
+        // no launch for a tile group without tiles or whose block is folded
+        // already, or before the first block is complete (a captured push keeps its launch, which then exits at
         // once: it replays at any push count; timed pushes keep theirs too)
         const Group &g = c->groups[(size_t)i];
         const int64_t S = c->n_push + 1;
         if (st == c->stream && !c->d_stamps &&
-            (S < g.T || (S % g.T) * g.tiles_per_group >= g.n_tiles))
+            (S < g.T || (S % g.T) * g.tiles_per_group >= g.n_tiles ||
+             g.flushed[(size_t)(S % g.T)] >= S / g.T))
             continue;
         DeferredArgs da = deferred_args(c, i);
         da.stamps = c->d_stamps; // the catch-up flushes of a readout carry none
@@ -439,27 +450,54 @@ void mirror_flushes(corr_ctx *c, int64_t S)
     }
 }
 
-// Fold block q of group gi in every tile group that has not folded it yet, one
-// launch, and record it.
-int fold_all(corr_ctx *c, const std::vector<int> &idx, int64_t q)
+// Record that every tile group of the groups idx has folded block q, and
+// advance the counters by the pushes this stands for.
+int commit_block(corr_ctx *c, const std::vector<int> &idx, int64_t q, int32_t advance, bool stamps)
 {
+    for (int i : idx)
+        for (int64_t &f : c->groups[(size_t)i].flushed) f = std::max(f, q);
+    if (!c->counted) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
     pe.step2 = c->d_step_side;
-    pe.advance = 0;
+    pe.advance = advance;
     pe.commit_block = q;
+    if (stamps) {
+        pe.stamps = c->d_stamps;
+        pe.n_stamps = 2;
+    }
     for (int i : idx) {
-        DeferredArgs da = deferred_args(c, i);
-        da.fixed_group = -2;
-        da.fixed_block = q;
-        HIP_TRY(c, launch_flush_fold(da, c->stream));
         pe.defer_t[pe.n_flushed] = c->groups[(size_t)i].T;
         pe.flushed[pe.n_flushed++] = c->groups[(size_t)i].d_flushed;
     }
     HIP_TRY(c, launch_push_end(pe, c->stream));
-    for (int i : idx)
-        for (int64_t &f : c->groups[(size_t)i].flushed) f = std::max(f, q);
     return CORR_OK;
+}
+
+// Fold block q of the groups idx in every tile group that has not folded it
+// yet (one launch for each run of such tile groups: the scheduled folds go
+// through them in order, so there is one run), and record it.
+int fold_all(corr_ctx *c, const std::vector<int> &idx, int64_t q)
+{
+    for (int i : idx) {
+        const Group &g = c->groups[(size_t)i];
+        for (int j = 0; j < g.T;) {
+            if (g.flushed[(size_t)j] >= q) {
+                ++j;
+                continue;
+            }
+            int j1 = j;
+            while (j1 < g.T && g.flushed[(size_t)j1] < q) ++j1;
+            DeferredArgs da = deferred_args(c, i);
+            da.fixed_group = -2;
+            da.fixed_block = q;
+            da.tile_first = std::min(g.n_tiles, j * g.tiles_per_group);
+            da.tile_end = std::min(g.n_tiles, j1 * g.tiles_per_group);
+            if (da.tile_end > da.tile_first) HIP_TRY(c, launch_flush_fold(da, c->stream));
+            j = j1;
+        }
+    }
+    return commit_block(c, idx, q, 0, false);
 }
 
 // Before a readout: fold the last complete block in the tile groups that have
@@ -498,11 +536,12 @@ bool is_split(const GroupArgs &g)
 
 // Push kernel launch(es) for the groups of one set (batched: one launch;
 // per-group form: one launch per group; long one-level windows: one window
-// launch each), all reading the push counter of the set's arguments.
-int launch_set(corr_ctx *c, const PushArgs &base, const std::vector<int> &idx,
+// launch each), all for the push after `step`.
+int launch_set(corr_ctx *c, const PushArgs &base, StepRef step, const std::vector<int> &idx,
                const std::vector<const void *> &resolved, hipStream_t st)
 {
     PushArgs a = base;
+    a.step = step;
     for (size_t j = 0; j < idx.size(); ++j) a.g[j].samples = resolved[(size_t)idx[j]];
     const int cpt = c->tuning.chans_per_thread, lch = c->tuning.lag_chunk;
     const int block = c->tuning.tile_channels / cpt;
@@ -519,26 +558,26 @@ int launch_set(corr_ctx *c, const PushArgs &base, const std::vector<int> &idx,
             if (!is_window_deferred(a.g[i])) continue;
             if (pending >= 0 && !(c->flags & CORR_FLAG_PER_GROUP) &&
                 window_folds_share_launch(a.g[pending], a.g[i])) {
-                HIP_TRY(c, launch_window_fold2(a.g[pending], a.g[i], base.step, st));
+                HIP_TRY(c, launch_window_fold2(a.g[pending], a.g[i], step, st));
                 pending = -1;
                 continue;
             }
-            if (pending >= 0) HIP_TRY(c, launch_window_fold(a.g[pending], base.step, st));
+            if (pending >= 0) HIP_TRY(c, launch_window_fold(a.g[pending], step, st));
             pending = i;
         }
-        if (pending >= 0) HIP_TRY(c, launch_window_fold(a.g[pending], base.step, st));
+        if (pending >= 0) HIP_TRY(c, launch_window_fold(a.g[pending], step, st));
         for (int i = 0; i < a.n_groups; ++i) {
             if (is_window_deferred(a.g[i])) continue;
             if (is_window(a.g[i])) {
-                HIP_TRY(c, launch_push_window(a.g[i], base.step, cpt, lch, block, kWindowLags, st));
+                HIP_TRY(c, launch_push_window(a.g[i], step, cpt, lch, block, kWindowLags, st));
                 continue;
             }
             if (a.g[i].pair) { // pair groups have their own kernels
-                HIP_TRY(c, launch_push_group(a.g[i], base.step, cpt, lch, block, st));
+                HIP_TRY(c, launch_push_group(a.g[i], step, cpt, lch, block, st));
                 continue;
             }
             if (!(c->flags & CORR_FLAG_PER_GROUP) && is_split(a.g[i])) {
-                HIP_TRY(c, launch_push_split(a.g[i], base.step, cpt, lch, block, kSplitLags, st));
+                HIP_TRY(c, launch_push_split(a.g[i], step, cpt, lch, block, kSplitLags, st));
                 continue;
             }
             rest.g[n] = a.g[i];
@@ -553,7 +592,7 @@ int launch_set(corr_ctx *c, const PushArgs &base, const std::vector<int> &idx,
     }
     if (c->flags & CORR_FLAG_PER_GROUP) {
         for (int i = 0; i < a.n_groups; ++i)
-            HIP_TRY(c, launch_push_group(a.g[i], base.step, cpt, lch, block, st));
+            HIP_TRY(c, launch_push_group(a.g[i], step, cpt, lch, block, st));
     } else {
         int64_t grid = c->tuning.grid_blocks > 0 ? c->tuning.grid_blocks : a.total_tiles;
         grid = std::min<int64_t>(grid, a.total_tiles);
@@ -622,7 +661,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     for (int i : dset) {
         GroupArgs ga = c->pargs.g[(size_t)i];
         ga.samples = resolved[(size_t)i];
-        HIP_TRY(c, launch_stage(ga, c->d_step, st));
+        HIP_TRY(c, launch_stage(ga, step_main(c), st));
     }
     hipStream_t pst = fork ? c->side_stream : st;
     for (int i : c->side_set) {
@@ -660,7 +699,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         // staging and the flush of the block-deferred groups
         std::vector<int> idx(c->main_set);
         idx.insert(idx.end(), c->side_set.begin(), c->side_set.end());
-        int rc = launch_set(c, c->pa_direct, idx, resolved, pst);
+        int rc = launch_set(c, c->pa_direct, step_side(c), idx, resolved, pst);
         if (rc != CORR_OK) return rc;
         if (chained) {
             PushEndArgs se{};
@@ -674,10 +713,10 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         }
     } else if (fork) {
         // no flush to overlap: the sample-fed groups run beside the producers
-        int rc = launch_set(c, c->pa_side, c->side_set, resolved, pst);
+        int rc = launch_set(c, c->pa_side, step_side(c), c->side_set, resolved, pst);
         if (rc != CORR_OK) return rc;
         HIP_TRY(c, hipEventRecord(c->ev_join, pst));
-        rc = launch_set(c, c->pa_main, c->main_set, resolved, st);
+        rc = launch_set(c, c->pa_main, step_main(c), c->main_set, resolved, st);
         if (rc != CORR_OK) return rc;
     } else {
         std::vector<int> idx(c->main_set);
@@ -689,7 +728,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
                 HIP_TRY(c, hipStreamWaitEvent(c->side_stream, c->ev_fork, 0));
                 ust = c->side_stream;
             }
-            int rc = launch_set(c, c->pa_direct, idx, resolved, ust);
+            int rc = launch_set(c, c->pa_direct, step_side(c), idx, resolved, ust);
             if (rc != CORR_OK) return rc;
             if (fork_updates) HIP_TRY(c, hipEventRecord(c->ev_join, ust));
         }
@@ -706,6 +745,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     if (fork_updates) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     if (fork && !chained) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (!c->counted) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
     pe.step2 = chained ? nullptr : c->d_step_side;
@@ -833,6 +873,7 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
     c->device = device;
     c->stream = static_cast<hipStream_t>(stream);
     c->flags = flags;
+    c->counted = (flags & (CORR_FLAG_GRAPH | CORR_FLAG_TIMING)) != 0;
     c->tuning = tn;
     c->fold_threads = tn.fold_threads ? tn.fold_threads : kFoldThreadsDefault;
     DeviceGuard dg(device);
@@ -1251,10 +1292,6 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
         CREATE_HIP(hipMalloc(&c->d_stamps, 2 * sizeof(FoldStamps)));
         CREATE_HIP(hipMemcpy(c->d_stamps, init.data(), 2 * sizeof(FoldStamps), hipMemcpyHostToDevice));
     }
-    c->pargs.step = c->d_step;
-    c->pa_main.step = c->d_step;
-    c->pa_side.step = c->d_step_side; // the sets that run on the side stream
-    c->pa_direct.step = c->d_step_side;
     CREATE_HIP(hipStreamSynchronize(c->stream));
 
     if (flags & CORR_FLAG_GRAPH) {
@@ -1470,30 +1507,19 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
                 DeferredArgs da = deferred_args(ctx, i);
                 da.fixed_group = -2;
                 da.fixed_block = q + 1;
+                da.tile_first = 0;
+                da.tile_end = da.g.n_tiles;
                 da.hist = static_cast<const char *>(samples[(size_t)i]) + (int64_t)r * stride[(size_t)i];
                 da.hist_stride = stride[(size_t)i];
                 da.stamps = ctx->d_stamps;
                 HIP_TRY(ctx, launch_history_fold(da, ctx->stream));
             }
-            PushEndArgs pe{};
-            pe.step = ctx->d_step;
-            pe.step2 = ctx->d_step_side;
-            pe.advance = others ? 0 : T; // the other groups' pushes advanced the counter
-            pe.commit_block = q + 1;
-            pe.stamps = ctx->d_stamps;
-            pe.n_stamps = 2;
-            for (int i : ctx->deferred_set) {
-                pe.defer_t[pe.n_flushed] = ctx->groups[(size_t)i].T;
-                pe.flushed[pe.n_flushed++] = ctx->groups[(size_t)i].d_flushed;
-            }
-            HIP_TRY(ctx, launch_push_end(pe, ctx->stream));
+            // (the other groups' pushes advanced the counter)
+            int rc = commit_block(ctx, ctx->deferred_set, q + 1, others ? 0 : T, true);
+            if (rc != CORR_OK) return rc;
             q += 1;
             r += T;
             if (!others) ctx->n_push += T;
-            for (int i : ctx->deferred_set) {
-                Group &g = ctx->groups[(size_t)i];
-                for (int j = 0; j < g.T; ++j) g.flushed[(size_t)j] = std::max(g.flushed[(size_t)j], q);
-            }
         }
     }
     while (r < n_steps) {
@@ -1733,7 +1759,7 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         }
         DeferredArgs da{};
         da.g = ctx->pargs.g[(size_t)group];
-        da.step = ctx->d_step;
+        da.step = StepRef{nullptr, S};
         da.ne = ne;
         da.ch_begin = cb;
         da.ch_end = ce;

@@ -163,7 +163,7 @@ __device__ __forceinline__ int wrap_slot(int64_t v, int p0)
 // kind and length share a launch; a single window passes itself twice).
 template <int K, int LB>
 __global__ __launch_bounds__(512) void window_fold_kernel(GroupArgs g0, GroupArgs g1, int x1,
-                                                          const int64_t *step, int lpb, int subs_per_block)
+                                                          StepRef step, int lpb, int subs_per_block)
 {
     using S = typename WK<K>::S;
     using A = typename WK<K>::A;
@@ -174,12 +174,12 @@ __global__ __launch_bounds__(512) void window_fold_kernel(GroupArgs g0, GroupArg
     extern __shared__ __align__(16) unsigned char win_lds[];
     S *const rows = reinterpret_cast<S *>(win_lds); // [row][64 channels]
 
-    // Push P = *step + 1: its sample goes to ring slot (P - 1) mod p0 (the
+    // Push P = pushes_before(step) + 1: its sample goes to ring slot (P - 1) mod p0 (the
     // first wave of each channel group's y = 0 block writes it; the blocks of
     // this launch that need value P read it from the input instead, and none
     // reads that slot for an older value: the oldest value folded is newer
     // than P - p0).  Then lag block j folds block q.
-    const int64_t P = *step + 1;
+    const int64_t P = pushes_before(step) + 1;
     const bool second = (int)blockIdx.x >= x1; // uniform over the block
     const int tw = second ? g1.tw : g0.tw;
     const int p0 = second ? g1.p0 : g0.p0;
@@ -313,7 +313,7 @@ template <int K, int LB> const void *window_kernel()
 // One launch of window g0 and, when g1 is given (same kind and length), of
 // window g1 in the blocks after g0's.
 template <int LB>
-hipError_t launch_fold_lb(const GroupArgs &g0, const GroupArgs *g1, const int64_t *step, hipStream_t st)
+hipError_t launch_fold_lb(const GroupArgs &g0, const GroupArgs *g1, StepRef step, hipStream_t st)
 {
     const WindowShape w = window_shape(g0, LB);
     const unsigned x1 = w.grid_x;
@@ -334,7 +334,7 @@ hipError_t launch_fold_lb(const GroupArgs &g0, const GroupArgs *g1, const int64_
     if (!fn) return hipErrorInvalidValue;
     GroupArgs ga = g0, gb = g1 ? *g1 : g0;
     int xs = (int)x1;
-    const int64_t *sp = step;
+    StepRef sp = step;
     int lpb = w.lpb, spb = w.subs_per_block;
     void *args[] = {&ga, &gb, &xs, &sp, &lpb, &spb};
     return hipLaunchKernel(fn, grid, block, args, lds, st);
@@ -348,7 +348,7 @@ bool window_fold_valid(const GroupArgs &g)
 // Eight lags per wave reuse each loaded value more; four give twice the waves,
 // which wins while the grid holds fewer than four waves per SIMD (a few
 // thousand channels, the k-space groups of long windows).
-hipError_t launch_fold(const GroupArgs &g0, const GroupArgs *g1, const int64_t *step, hipStream_t st)
+hipError_t launch_fold(const GroupArgs &g0, const GroupArgs *g1, StepRef step, hipStream_t st)
 {
     const WindowShape w8 = window_shape(g0, 8);
     const unsigned gx = w8.grid_x + (g1 ? window_shape(*g1, 8).grid_x : 0u);
@@ -367,7 +367,7 @@ bool window_deferred_supported(int kind)
 
 int window_lags_per_block(int p) { return (p + kWindowT - 1) / kWindowT; }
 
-hipError_t launch_window_fold(const GroupArgs &g, const int64_t *step, hipStream_t st)
+hipError_t launch_window_fold(const GroupArgs &g, StepRef step, hipStream_t st)
 {
     if (!window_fold_valid(g)) return hipErrorInvalidValue;
     return launch_fold(g, nullptr, step, st);
@@ -380,7 +380,7 @@ bool window_folds_share_launch(const GroupArgs &a, const GroupArgs &b)
     return a.kind == b.kind && a.p == b.p;
 }
 
-hipError_t launch_window_fold2(const GroupArgs &a, const GroupArgs &b, const int64_t *step, hipStream_t st)
+hipError_t launch_window_fold2(const GroupArgs &a, const GroupArgs &b, StepRef step, hipStream_t st)
 {
     if (!window_fold_valid(a) || !window_fold_valid(b) || !window_folds_share_launch(a, b))
         return hipErrorInvalidValue;
