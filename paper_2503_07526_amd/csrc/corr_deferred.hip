@@ -84,11 +84,71 @@ template <> struct Fold<K_F32_KAHAN> {
     static __device__ __forceinline__ double value(float h, float c) { return (double)h - (double)c; }
 };
 
-__device__ __forceinline__ double wave_sum(double v)
+// v of the lane whose index differs in one bit (8, 4, 2 or 1).
+template <int BIT> __device__ __forceinline__ double lane_xor(double v)
 {
+    union { double d; int w[2]; } u, o;
+    u.d = v;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
+    for (int i = 0; i < 2; ++i) {
+        if constexpr (BIT == 8) o.w[i] = __builtin_amdgcn_update_dpp(0, u.w[i], 0x128, 0xf, 0xf, true); // row_ror:8
+        else if constexpr (BIT == 4) o.w[i] = __builtin_amdgcn_ds_swizzle(u.w[i], 0x101f);            // xor 4
+        else if constexpr (BIT == 2) o.w[i] = __builtin_amdgcn_update_dpp(0, u.w[i], 0x4e, 0xf, 0xf, true);
+        else o.w[i] = __builtin_amdgcn_update_dpp(0, u.w[i], 0xb1, 0xf, 0xf, true);
+    }
+    return o.d;
+}
+
+// a of the lanes with the bit (32 or 16) clear and b of those with it set,
+// each added to the same value of the lane that differs in that bit.
+template <int BIT> __device__ __forceinline__ double pair_fold(double a, double b)
+{
+    union { double d; unsigned w[2]; } x, y;
+    x.d = a;
+    y.d = b;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if constexpr (BIT == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(x.w[i], y.w[i], false, false);
+            x.w[i] = r[0];
+            y.w[i] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane16_swap(x.w[i], y.w[i], false, false);
+            x.w[i] = r[0];
+            y.w[i] = r[1];
+        }
+    }
+    return x.d + y.d;
+}
+
+// Sums of N = 8 or 16 values over the wave's 64 lanes: lane l returns the sum
+// of v[l / (64 / N)].  Every sum is the binary tree over lane distances 32,
+// 16, .., 1, but after each exchange a lane carries on only half of the
+// values: 7 (or 15) exchanges and 3 (2) more instead of 6 for each value.
+template <int N> __device__ __forceinline__ double wave_sums(const double (&v)[N])
+{
+    static_assert(N == 8 || N == 16, "8 or 16 values");
+    const int lane = (int)(threadIdx.x & 63);
+    double a[N / 2], b[N / 4];
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) a[j] = pair_fold<32>(v[j], v[j + N / 2]);
+#pragma unroll
+    for (int j = 0; j < N / 4; ++j) b[j] = pair_fold<16>(a[j], a[j + N / 4]);
+    double c[N / 8];
+    const bool up8 = lane & 8;
+#pragma unroll
+    for (int j = 0; j < N / 8; ++j)
+        c[j] = (up8 ? b[j + N / 8] : b[j]) + lane_xor<8>(up8 ? b[j] : b[j + N / 8]);
+    double s;
+    if constexpr (N == 16) {
+        const bool up4 = lane & 4;
+        s = (up4 ? c[1] : c[0]) + lane_xor<4>(up4 ? c[0] : c[1]);
+    } else {
+        s = c[0] + lane_xor<4>(c[0]);
+    }
+    s += lane_xor<2>(s);
+    s += lane_xor<1>(s);
+    return s;
 }
 
 struct Ctx {
@@ -163,6 +223,9 @@ __device__ __forceinline__ void fold_level(Ctx &cx, int k, const typename RK<K>:
             if constexpr (NP == 2) __builtin_nontemporal_store(c[j], &lo[(size_t)j * tw + cx.lane]);
         }
     } else {
+        // All rows are loaded first (those of lags without a count too): with
+        // each load inside its lag's branch a wave waited for one row at a
+        // time, 7.2 ms for 1.2e7 channels after 556 pushes (11.8 GB) against 2.5.
         const DeferredArgs &a = *cx.a;
         const int64_t S = cx.f + cx.r;
         int64_t sk = S >> k;
@@ -171,87 +234,39 @@ __device__ __forceinline__ void fold_level(Ctx &cx, int k, const typename RK<K>:
         if (hi_lag <= l0) return;
         const int e0 = entry_offset<P>(k, S);
         const bool in_slice = cx.valid && cx.ch >= a.slice_begin && cx.ch < a.slice_end;
+        A h[NL], c[NL];
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            const int L = l0 + j;
-            if (L < hi_lag) {
-                A h = hi[(size_t)j * tw + cx.lane];
-                A c = A(0);
-                if constexpr (NP == 2) c = lo[(size_t)j * tw + cx.lane];
-                if (any_pending) Fold<K>::add(h, c, (A)part[j]);
-                const double v = Fold<K>::value(h, c);
-                const int e = e0 + j;
-                if (in_slice) a.slice_out[(size_t)(cx.ch - a.slice_begin) * a.ne + e] = v;
-                // Fixed-order sum over the wave's 64 consecutive channels (a
-                // chunk aligned to 64 whatever the tile width).
-                const double s = wave_sum(cx.reduce_me ? v : 0.0);
-                if ((threadIdx.x & 63) == 0)
-                    a.chunk_partial[(size_t)((cx.ch >> 6) - a.row_begin) * a.ne + e] = s;
-            }
+            h[j] = __builtin_nontemporal_load(&hi[(size_t)j * tw + cx.lane]);
+            if constexpr (NP == 2) c[j] = __builtin_nontemporal_load(&lo[(size_t)j * tw + cx.lane]); else c[j] = A(0);
         }
+        double v[NL];
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            if (any_pending) Fold<K>::add(h[j], c[j], (A)part[j]);
+            v[j] = Fold<K>::value(h[j], c[j]);
+        }
+        if (in_slice) {
+#pragma unroll
+            for (int j = 0; j < NL; ++j)
+                if (l0 + j < hi_lag) a.slice_out[(size_t)(cx.ch - a.slice_begin) * a.ne + e0 + j] = v[j];
+        }
+        // Fixed-order sums over the wave's 64 consecutive channels (a chunk
+        // aligned to 64 whatever the tile width).
+#pragma unroll
+        for (int j = 0; j < NL; ++j) v[j] = cx.reduce_me ? v[j] : 0.0;
+        const double s = wave_sums<NL>(v);
+        constexpr int W = 64 / NL;
+        const int j = (int)(threadIdx.x & 63) / W;
+        if ((threadIdx.x & (W - 1)) == 0 && l0 + j < hi_lag)
+            a.chunk_partial[(size_t)((cx.ch >> 6) - a.row_begin) * a.ne + e0 + j] = s;
     }
 }
 
-// Level 0: fold the r pending pushes (f, f + r] into the lag sums and form the
-// level-1 block means.  out[q] = mean of new values 2q, 2q+1.  The pushes are
-// taken in chunks of kL0Chunk with a sliding window of the P - 1 values
-// before each chunk, so that only P - 1 + kL0Chunk ring values are live.
+// Levels 0 and 1 take a block in chunks of kL0Chunk pushes.
 constexpr int kL0Chunk = 64;
 
-template <int K, int P, int T, bool READ>
-__device__ __forceinline__ void level0(Ctx &cx, typename RK<K>::S (&out)[T / 2])
-{
-    using S = typename RK<K>::S;
-    using PT = typename RK<K>::PT;
-    constexpr int C = T < kL0Chunk ? T : kL0Chunk;
-    static_assert(T % C == 0 && C % 2 == 0, "chunks of whole pairs");
-    const DeferredArgs &a = *cx.a;
-    const GroupArgs &g = a.g;
-    const int tw = g.tw;
-    const int P0 = g.p0;
-    const S *ring = reinterpret_cast<const S *>(cx.tb);
-    const int64_t f = cx.f;
-    const int r = cx.r;
-    // W: old values f-P+2 .. f, then the chunk's new values (zeros beyond r);
-    // value j sits in slot (j - 1) mod P0, and P - 1 + T < P0, so one modulo
-    // and a wrap per row suffice
-    S W[P - 1 + C];
-    const int slot0 = (int)((f - (P - 2) - 1 + P0) % P0);
-    auto row = [&](int i) -> S { // i-th value from f - P + 2
-        int slot = slot0 + i;
-        if (slot >= P0) slot -= P0;
-        return __builtin_nontemporal_load(&ring[(size_t)slot * tw + cx.lane]);
-    };
-#pragma unroll
-    for (int i = 0; i < P - 1; ++i) W[i] = row(i);
-    PT part[P];
-#pragma unroll
-    for (int L = 0; L < P; ++L) part[L] = PT(0);
-#pragma unroll
-    for (int c0 = 0; c0 < T; c0 += C) {
-        // keep the next chunk's loads after this chunk's products (otherwise
-        // they are hoisted and every chunk's values are live at once)
-        if (c0 > 0) asm volatile("" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < C; ++q) W[P - 1 + q] = c0 + q < r ? row(P - 1 + c0 + q) : S(0);
-#pragma unroll
-        for (int q = 0; q < C; ++q) {
-            if (c0 + q < r) {
-                const S x = W[P - 1 + q];
-#pragma unroll
-                for (int L = 0; L < P; ++L) pmac(part[L], x, W[P - 1 + q - L]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < C / 2; ++q)
-            out[c0 / 2 + q] = (W[P - 1 + 2 * q] + W[P + 2 * q]) / S(2);
-#pragma unroll
-        for (int i = 0; i < P - 1; ++i) W[i] = W[i + C];
-    }
-    fold_level<K, P, P, READ>(cx, 0, part, r > 0);
-}
-
-// Levels 0 and 1 together, for blocks of more than kL0Chunk pushes: the r
+// Levels 0 and 1 together: the r
 // pending pushes are taken in chunks of kL0Chunk; each chunk adds its level-0
 // lag products, forms its kL0Chunk / 2 level-1 means, adds their level-1 lag
 // products at once (sliding windows of the P - 1 older values of both levels
@@ -313,8 +328,25 @@ __device__ __forceinline__ void levels01(Ctx &cx, typename RK<K>::S *out)
     // one chunk at a time (a rolled loop: only one chunk's values are live)
 #pragma unroll 1
     for (int c0 = 0; c0 < T; c0 += C) {
+        if constexpr (READ) {
+            if (c0 >= r) break; // the cascade takes r / 4 level-2 values
+            // rows by eights (the last ones past r, read and put to zero)
 #pragma unroll
-        for (int q = 0; q < C; ++q) W0[P - 1 + q] = c0 + q < r ? newval(c0 + q) : S(0);
+            for (int q0 = 0; q0 < C; q0 += 8) {
+                if (c0 + q0 < r) {
+#pragma unroll
+                    for (int q = q0; q < q0 + 8; ++q) W0[P - 1 + q] = newval(c0 + q);
+                } else {
+#pragma unroll
+                    for (int q = q0; q < q0 + 8; ++q) W0[P - 1 + q] = S(0);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q) W0[P - 1 + q] = c0 + q < r ? W0[P - 1 + q] : S(0);
+        } else {
+#pragma unroll
+            for (int q = 0; q < C; ++q) W0[P - 1 + q] = newval(c0 + q);
+        }
 #pragma unroll
         for (int q = 0; q < C; ++q) {
             if (c0 + q < r) {
@@ -392,11 +424,16 @@ __device__ __forceinline__ void level_k(Ctx &cx, int k, const typename RK<K>::S 
     S *ring = reinterpret_cast<S *>(cx.tb + g.lvl0_bytes + (int64_t)(k - 1) * g.lvlk_bytes);
     const int64_t fk = cx.f >> k; // level-k values already in the ring
     S H[P - 1 + N];
+    if (!READ || n_in > 0) { // a readout needs the older values for new products only
 #pragma unroll
-    for (int i = 0; i < P - 1; ++i) {
-        const int64_t v = fk - (P - 2) + i; // value number (1-based)
-        const int slot = (int)((v - 1 + P) % P);
-        H[i] = __builtin_nontemporal_load(&ring[(size_t)slot * tw + cx.lane]);
+        for (int i = 0; i < P - 1; ++i) {
+            const int64_t v = fk - (P - 2) + i; // value number (1-based)
+            const int slot = (int)((v - 1 + P) % P);
+            H[i] = __builtin_nontemporal_load(&ring[(size_t)slot * tw + cx.lane]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < P - 1; ++i) H[i] = S(0);
     }
 #pragma unroll
     for (int q = 0; q < N; ++q) H[P - 1 + q] = q < n_in ? in[q] : S(0);
@@ -445,6 +482,9 @@ __device__ __forceinline__ void cascade(Ctx &cx, int k, const typename RK<K>::S 
     using S = typename RK<K>::S;
     const int b = cx.a->g.levels;
     if (k >= b) return;
+    if constexpr (READ) {
+        if (((cx.f + cx.r) >> k) <= P / 2) return; // no lag of this level or a coarser one has a count
+    }
     if constexpr (N >= 2) {
         S out[N / 2];
         int n_out;
@@ -454,7 +494,7 @@ __device__ __forceinline__ void cascade(Ctx &cx, int k, const typename RK<K>::S 
         S cur[1] = {in[0]};
         int n = n_in;
         for (int kk = k; kk < b; ++kk) {
-            if (n == 0 && !READ) break;
+            if (READ ? ((cx.f + cx.r) >> kk) <= P / 2 : n == 0) break;
             S nxt[1];
             int nn;
             level_k<K, P, 1, READ>(cx, kk, cur, n, nxt, nn);
@@ -527,23 +567,18 @@ __device__ __forceinline__ void deferred_pass(const DeferredArgs &a)
         cx.ch = tile * g.tw + cx.lane;
         cx.valid = cx.ch < g.n_ch;
         cx.reduce_me = cx.valid && cx.ch >= a.ch_begin && cx.ch < a.ch_end;
-        if constexpr (T > kL0Chunk) {
-            // levels 0 and 1 streamed chunk by chunk, then the cascade from
-            // level 2 (f is a multiple of T, so level-1 pairs align); each
-            // thread reads back only its own column of l2s
-            using S = typename RK<K>::S;
-            __shared__ S l2s[(T / 4) * NT];
-            levels01<K, P, T, READ, HIST>(cx, l2s);
-            S l2[T / 4];
+        // levels 0 and 1 streamed chunk by chunk, then the cascade from level
+        // 2 (f is a multiple of T, so level-1 pairs align); each thread reads
+        // back only its own column of l2s
+        static_assert(T % kL0Chunk == 0, "whole chunks");
+        using S = typename RK<K>::S;
+        __shared__ S l2s[(T / 4) * NT];
+        levels01<K, P, T, READ, HIST>(cx, l2s);
+        S l2[T / 4];
 #pragma unroll
-            for (int q = 0; q < T / 4; ++q) l2[q] = l2s[(size_t)q * blockDim.x + threadIdx.x];
-            cascade<K, P, T / 4, READ>(cx, 2, l2, (r / 2) / 2);
-        } else {
-            static_assert(!HIST, "history folds take blocks of more than kL0Chunk pushes");
-            typename RK<K>::S l1[T / 2];
-            level0<K, P, T, READ>(cx, l1);
-            cascade<K, P, T / 2, READ>(cx, 1, l1, r / 2);
-        }
+        for (int q = 0; q < T / 4; ++q)
+            l2[q] = !READ || q < (r / 2) / 2 ? l2s[(size_t)q * blockDim.x + threadIdx.x] : S(0);
+        cascade<K, P, T / 4, READ>(cx, 2, l2, (r / 2) / 2);
     }
 }
 
@@ -578,6 +613,23 @@ __global__ __launch_bounds__(kFoldThreadsDefault) void deferred_read_kernel(Defe
 // row_begin on), then the groups in order.
 constexpr int kColGroup = 1024;
 
+// Sum of v[i stride], i = 0 .. n - 1, in order, the loads kColLoads at a time
+// ahead of the additions (one after the other they took the latency of each:
+// 400 us for the 1024 rows of a group).
+constexpr int kColLoads = 32;
+__device__ __forceinline__ double ordered_sum(const double *v, int64_t stride, int64_t n)
+{
+    double s = 0.0;
+    for (int64_t i = 0; i < n; i += kColLoads) {
+        double x[kColLoads];
+#pragma unroll
+        for (int u = 0; u < kColLoads; ++u) x[u] = v[(i + u < n ? i + u : n - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < kColLoads; ++u) s += i + u < n ? x[u] : 0.0; // (s is never -0)
+    }
+    return s;
+}
+
 __global__ void colsum_group_kernel(const double *rows, int64_t row_begin, int64_t n_rows, int ne,
                                     int64_t group_begin, double *groups)
 {
@@ -587,18 +639,14 @@ __global__ void colsum_group_kernel(const double *rows, int64_t row_begin, int64
     const int64_t r0 = grp * kColGroup;
     int64_t r1 = r0 + kColGroup;
     if (r1 > n_rows) r1 = n_rows;
-    double s = 0.0;
-    for (int64_t r = r0; r < r1; ++r) s += rows[(size_t)(r - row_begin) * ne + e];
-    groups[(size_t)grp * ne + e] = s;
+    groups[(size_t)grp * ne + e] = ordered_sum(rows + (size_t)(r0 - row_begin) * ne + e, ne, r1 - r0);
 }
 
 __global__ void colsum_final_kernel(const double *groups, int64_t n_groups, int ne, double *out)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= ne) return;
-    double s = 0.0;
-    for (int64_t q = 0; q < n_groups; ++q) s += groups[(size_t)q * ne + e];
-    out[e] = s;
+    out[e] = ordered_sum(groups + e, ne, n_groups);
 }
 
 template <int K, int P, int T, int NT, bool READ, bool HIST>

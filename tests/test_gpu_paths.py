@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from tests.gpu_helpers import TOL, say
+from tests.gpu_helpers import TOL, ou_inputs, say
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
@@ -61,3 +61,36 @@ def test_fold_subsets(corrmod, n, graph):
             for i, ch in enumerate(pick):
                 r = c.finalize(0, slice_=(ch, ch + 1))
                 _check_channels(r, o, [(0, i)], TOL[("f32", "kahan")], f"S={s} channel {ch}")
+
+
+@pytest.mark.parametrize("accum", ["kahan", "f64", "f32"])
+@pytest.mark.parametrize("block", [256, 128])
+def test_readout_of_pending_pushes(corrmod, accum, block):
+    """Readouts of a block-deferred group with 0 .. block - 1 pushes after the
+    last block (both sides of every eight rows and of every chunk of 64), at
+    counts where a level has its first lags (8 and 9 values) or none, over all
+    channels, a channel range and a slice."""
+    say(f"[pending readout] accum={accum} block={block}")
+    n, levels = 197, 8
+    stops = [1, 7, 8, 9, 16, 17, 63, 64, 65, 71, 72, 73, 127, 128, 129, 136, 191, 192, 193, 200,
+             255, 256, 257, 264, 319, 320, 321, 383, 384, 447, 448, 511, 512, 513, 575, 576, 577]
+    x = ou_inputs(31, 1, n, stops[-1], "f32")
+    xt = torch.from_numpy(x).cuda()
+    o = oracle.OracleCorrelator(n, levels, 16, 2)
+    tuning = dict(tile_channels=256, chans_per_thread=2, lag_chunk=8, grid_blocks=0, fold_block=block)
+    tol = TOL[("f32", accum)]
+    with corrmod.Correlator([corrmod.GroupDesc(n, levels, 16, 2, dtype="f32", accum=accum)],
+                            tuning=tuning) as c:
+        s = 0
+        for stop in stops:
+            while s < stop:
+                c.push([xt[s]])
+                o.push(x[s].astype(np.float64))
+                s += 1
+            r = c.finalize(0, slice_=(60, 70))
+            _check_channels(r, o, [(i, 60 + i) for i in range(10)], tol, f"S={s}")
+            for b, e in ((0, n), (63, 130)):
+                r = c.finalize(0, ch=(b, e))
+                _, ref, _ = o.readout(b, e)
+                err = np.max(np.abs(r["c"] - ref)) / abs(ref[0])
+                assert err <= tol, f"S={s} channels [{b}, {e}): {err:.3e} > {tol:.1e}"
