@@ -27,6 +27,7 @@ hipError_t launch_momentum(const MomentumArgs &a, hipStream_t st); // partial + 
 int momentum_blocks(int64_t n_atoms); // blocks of the partial kernel (size of the partial buffer)
 hipError_t rhok_mfma_prepare(int table_rows, int nw, int nmax); // once per context, before the first launch
 int rhok_mfma_chunks(int n_mtiles, int nw); // blocks along the M tiles (grid.x)
+int rhok_mfma_blocks_per_cu(int n_mtiles, int nw, int table_rows); // blocks that share a compute unit
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st);
 bool deferred_supported(int kind, int p, int m);
 hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st);

@@ -1166,12 +1166,30 @@ int rhok_mfma_chunks(int n_mtiles, int nw)
     return (n_mtiles + maxt - 1) / maxt;
 }
 
+// Contraction waves of a couple block (one more wave builds Z).
+static int couple_cwaves(int n_mtiles)
+{
+    const int chunks = rhok_mfma_chunks(n_mtiles, 1);
+    const int per_chunk = (n_mtiles + chunks - 1) / chunks;
+    const int cwaves = (per_chunk + kCpTilesPerWave - 1) / kCpTilesPerWave;
+    return cwaves < kCpMinCWaves ? kCpMinCWaves : cwaves;
+}
+
+// The current producer's 8 waves of about 200 registers and a couple block of
+// more than 8 waves fill a CU (2048 k-vectors: 12 waves, 512 blocks slower
+// than 256).  Two smaller couple blocks (118 registers) share it, which hides
+// the barriers of each other's tiles: a push of 1e6 atoms at 50, 300 and 1000
+// k-vectors 68, 78 and 88 -> 48, 57 and 74 us, of 2e5 atoms at 300 30 -> 28
+// us.  Three (50 k-vectors: 5 waves) took 60 us instead of 48.
+int rhok_mfma_blocks_per_cu(int n_mtiles, int nw, int table_rows)
+{
+    return nw == 1 && couple_cwaves(n_mtiles) + 1 <= 8 && 2 * couple_lds_bytes(table_rows) <= kLdsBytes ? 2 : 1;
+}
+
 static hipError_t launch_couples(const RhokMfmaArgs &a, hipStream_t st)
 {
     const int chunks = rhok_mfma_chunks(a.n_mtiles, 1);
-    const int per_chunk = (a.n_mtiles + chunks - 1) / chunks;
-    int cwaves = (per_chunk + kCpTilesPerWave - 1) / kCpTilesPerWave;
-    if (cwaves < kCpMinCWaves) cwaves = kCpMinCWaves;
+    const int cwaves = couple_cwaves(a.n_mtiles);
     const size_t lds = couple_lds_bytes(a.x_rows + a.y_rows);
     if (a.early_loads)
         hipLaunchKernelGGL(rhok_couple_kernel<true>, dim3((unsigned)chunks, (unsigned)a.n_atom_blocks),

@@ -1019,14 +1019,6 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
                 for (int q = 0; q < nk; ++q) pair_ix.emplace(row_key(q), 0);
                 const int n_pairs = (int)pair_ix.size();
                 const int n_mtiles = (n_pairs + per_tile - 1) / per_tile;
-                // The matrix-core producer runs fastest with one block per
-                // compute unit (its double-buffered LDS tables and one wave
-                // per M tile fill a CU): CUs / M-tile chunks atom blocks.
-                int n_cu = 0;
-                CREATE_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
-                const int per_cu = std::max(1, n_cu / rhok_mfma_chunks(n_mtiles, g.nw));
-                n_ab = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(512, per_cu),
-                                                                   g.d.n_atoms / 1024));
                 const int ncol = rhok_mfma_cols();
                 // table rows: the n_x and n_y (couples: |n_y|) ranges of the
                 // rows (padding rows take the first row of each)
@@ -1038,6 +1030,18 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
                     y_hi = std::max(y_hi, row_key(q).second);
                 }
                 if (couples) y_lo = 0; // Y planes hold |n_y| = 0 .. y_hi
+                // Atom blocks: as many as the compute units hold at once (one
+                // each for large k-sets, rhok_mfma_blocks_per_cu), each of at
+                // least one 128-atom tile: a block takes its tiles one after
+                // the other, 2-3 us each, so at least 1000 atoms a block left
+                // most of the chip idle for small cells (n(k) of 20011 atoms
+                // at 300 k-vectors 23 -> 8 us with 157 blocks instead of 19).
+                int n_cu = 0;
+                CREATE_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
+                const int slots = n_cu * rhok_mfma_blocks_per_cu(n_mtiles, g.nw, (x_hi - x_lo + 1) + (y_hi - y_lo + 1)) /
+                                  rhok_mfma_chunks(n_mtiles, g.nw);
+                n_ab = (int)std::max<int64_t>(1, std::min<int64_t>(slots,
+                                                                   (g.d.n_atoms + 127) / 128));
                 std::vector<int32_t> pnx((size_t)n_mtiles * per_tile, x_lo), pny((size_t)n_mtiles * per_tile, y_lo);
                 int u = 0;
                 for (auto &e : pair_ix) {

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+import synth
 from tests.gpu_helpers import TOL, ou_inputs, say
 
 pytestmark = [pytest.mark.gpu,
@@ -94,3 +95,32 @@ def test_readout_of_pending_pushes(corrmod, accum, block):
                 _, ref, _ = o.readout(b, e)
                 err = np.max(np.abs(r["c"] - ref)) / abs(ref[0])
                 assert err <= tol, f"S={s} channels [{b}, {e}): {err:.3e} > {tol:.1e}"
+
+
+@pytest.mark.parametrize("source", ["rhok", "currents"])
+@pytest.mark.parametrize("atoms", [127, 128, 129, 4097, 32768, 32769, 98305, 100001])
+def test_producer_atom_blocks(corrmod, source, atoms):
+    """Atom blocks of one 128-atom tile, of less than one, of two with a nearly
+    empty second, and more blocks than compute units (small k-sets share
+    them): C(0) of one push against the oracle's direct double sums, for a small
+    k-set and one whose blocks need a compute unit each."""
+    box = 40.0
+    rng = np.random.default_rng(atoms)
+    x = rng.uniform(0, box, (1, 3, atoms)).astype(np.float32)
+    v = rng.standard_normal((1, 3, atoms)).astype(np.float32)
+    for nk in (24, 900) if atoms < 5000 else (24,):
+        say(f"[atom blocks] {source} atoms={atoms} nk={nk}")
+        kv = synth.kvectors(nk)
+        if source == "rhok":
+            inp, ref = x, oracle.rhok(x[0], kv, box)
+        else:
+            inp = np.concatenate([x, v], 1)
+            ref = oracle.currents(x[0], v[0], kv, box).reshape(-1)
+        expect = np.abs(ref) ** 2 / atoms
+        g = corrmod.GroupDesc(len(expect), 2, 4, 2, dtype="cf32", accum="f64", source=source, kvec=kv,
+                              n_atoms=atoms, box=box)
+        with corrmod.Correlator([g]) as c:
+            c.push([torch.from_numpy(np.ascontiguousarray(inp[0])).cuda()])
+            got = c.finalize(0, slice_=(0, len(expect)))["c_per_channel"][:, 0]
+        err = np.max(np.abs(got - expect)) / np.max(expect)
+        assert err < 2e-6, f"{source} atoms={atoms} nk={nk}: {err:.2e}"
