@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcorr_gfx950.so")
 HIPCC = "/opt/rocm/bin/hipcc"
 
-SOURCES = ["corr_push.hip", "corr_deferred.hip", "corr_rhok.hip", "corr_rhok_mfma.hip",
+SOURCES = ["corr_push.hip", "corr_multi.hip", "corr_deferred.hip", "corr_rhok.hip", "corr_rhok_mfma.hip",
            "corr_reduce.hip", "corr_window.hip", "corr_momentum.hip", "corr_runtime.cpp",
            "corr_autotune.cpp"]
 

@@ -85,6 +85,8 @@ constexpr int kFlushGroups = kDeferT;
 // pushes and a readout 8.8, 8.6, 8.2, 7.3 and 7.3 ms.  Beyond 256 x 98304
 // channels every push folds one group in any case.
 constexpr int64_t kFoldMinChannels = 98304;
+// Pushes that a multi-step pass of a per-step group adds at most (corr_multi.hip).
+constexpr int kMultiT = 64;
 // Threads per block of the fold kernels (the scheduled flush takes 64, 128 or
 // 256; a tile wider than a block is split over several blocks).
 constexpr int kFoldThreadsDefault = 128;
@@ -180,6 +182,20 @@ struct PushArgs {
     int32_t pad_;
     int64_t total_tiles;
     StepRef step;        // pushes completed before this one
+};
+
+// One push's samples of a group, copied to a row where they wait for a
+// multi-step pass.
+struct KeepRow {
+    const void *src;
+    void *dst;
+    int64_t bytes;
+    int64_t wide; // both ends 16-byte aligned (set by the launcher)
+};
+struct KeepArgs {
+    KeepRow row[kMaxGroups];
+    int32_t n;
+    int32_t pad_;
 };
 
 // Number of accumulator planes of a kind (2 for compensated sums).

@@ -16,6 +16,12 @@ hipError_t launch_push_window(const GroupArgs &g, StepRef step, int cpt, int lch
                               int block, int lags_per_block, hipStream_t st);
 hipError_t launch_push_split(const GroupArgs &g, StepRef step, int cpt, int lch, int block,
                              int lags_per_block, hipStream_t st);
+bool multi_supported(int kind, int p, int m, bool pair);
+// n pushes (1 .. kMultiT) of a per-step group after `step`, push s read at
+// rows + s stride.
+hipError_t launch_multi_push(const GroupArgs &g, StepRef step, const void *rows, int64_t stride, int n,
+                             hipStream_t st);
+hipError_t launch_keep_rows(const KeepArgs &a, hipStream_t st);
 hipError_t launch_push_end(const PushEndArgs &a, hipStream_t st); // flush records + step counter
 hipError_t launch_rhok(const RhokArgs &a, hipStream_t st);
 int rhok_tile_atoms(int nmax);

@@ -70,6 +70,11 @@ struct Group {
                            // push, one lag block folded per push)
     int p0 = 0;            // ring rows of level 0
     bool pair = false;     // channels correlate (x, y) pairs
+    // per-step group whose pushes wait in rows [kMultiT] of row_bytes each
+    // until a multi-step pass adds them (corr_ctx::waiting of them)
+    bool multi = false;
+    char *rows = nullptr;
+    int64_t row_bytes = 0;
     int64_t *d_flushed = nullptr;                // [kFlushGroups] blocks folded per tile group (T used)
     std::vector<int64_t> flushed;                // host mirror of d_flushed
     int64_t tiles_per_group = 0;
@@ -135,7 +140,11 @@ struct corr_ctx {
     // main_set: per-step (direct) groups fed with samples; side_set: k-density
     // groups; deferred_set (below): block-deferred groups (staged per push).
     std::vector<int> main_set, side_set; // context group indices
-    PushArgs pa_main{}, pa_side{}, pa_direct{}; // pa_direct: main_set + side_set
+    // groups updated by multi-step passes, and how many pushes wait in their
+    // rows; main_upd, side_upd: the others of main_set and side_set
+    std::vector<int> multi_set, main_upd, side_upd;
+    int32_t waiting = 0;
+    PushArgs pa_main{}, pa_side{}, pa_direct{}; // of main_upd, side_upd and both
     hipStream_t side_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     hipGraph_t graph = nullptr;
@@ -321,6 +330,7 @@ void free_group(Group &g)
     if (g.state) (void)hipFree(g.state);
     if (g.own_input) (void)hipFree(g.own_input);
     if (g.rhok_out) (void)hipFree(g.rhok_out);
+    if (g.rows) (void)hipFree(g.rows);
     if (g.d_seg) (void)hipFree(g.d_seg);
     if (g.d_partial) (void)hipFree(g.d_partial);
     if (g.d_mtab) (void)hipFree(g.d_mtab);
@@ -602,6 +612,20 @@ int launch_set(corr_ctx *c, const PushArgs &base, StepRef step, const std::vecto
     return CORR_OK;
 }
 
+// Groups with waiting pushes: add them (n_done: pushes issued, those
+// included).  On the context's stream.
+int add_waiting(corr_ctx *c, int64_t n_done)
+{
+    if (c->waiting == 0) return CORR_OK;
+    for (int i : c->multi_set) {
+        const Group &g = c->groups[(size_t)i];
+        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{nullptr, n_done - c->waiting}, g.rows, g.row_bytes,
+                                     c->waiting, c->stream));
+    }
+    c->waiting = 0;
+    return CORR_OK;
+}
+
 // Issue one push of every group on stream `st` with the given per-group
 // sample pointers (already resolved, never NULL).  Order on the main stream:
 // staging of block-deferred groups, the producers, the per-step push of the
@@ -632,16 +656,25 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     if (skip_deferred) with_flush = false;
     const size_t ng = c->groups.size();
     std::vector<const void *> resolved(ng);
-    for (size_t i = 0; i < ng; ++i)
-        resolved[i] = c->groups[i].produced() ? c->groups[i].rhok_out : src[i];
+    std::vector<void *> made(ng, nullptr); // where the producers write
+    KeepArgs keep{};
+    for (size_t i = 0; i < ng; ++i) {
+        const Group &g = c->groups[i];
+        char *row = g.multi ? g.rows + (int64_t)c->waiting * g.row_bytes : nullptr;
+        if (g.produced())
+            made[i] = row ? row : g.rhok_out;
+        else if (row)
+            keep.row[keep.n++] = KeepRow{src[i], row, (int64_t)g.input_bytes, 0};
+        resolved[i] = g.produced() ? made[i] : src[i];
+    }
     // Events are only recorded on direct launches, never while capturing, on
     // one push in timing_stride.
     const bool timed = (c->flags & CORR_FLAG_TIMING) && st == c->stream &&
                        c->n_push % c->timing_stride == 0;
     const bool fork = c->tuning.overlap_producers == 1 && !c->side_set.empty() &&
-                      (!c->main_set.empty() || !dset.empty());
+                      (!c->main_upd.empty() || !dset.empty());
     const bool fork_updates = c->tuning.overlap_producers == 2 && with_flush && !dset.empty() &&
-                              (!c->main_set.empty() || !c->side_set.empty());
+                              (!c->main_upd.empty() || !c->side_upd.empty());
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         int rc = next_events(c, 0, &e0, &e1);
@@ -658,6 +691,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         HIP_TRY(c, hipEventRecord(c->ev_fork, st));
         HIP_TRY(c, hipStreamWaitEvent(c->side_stream, c->ev_fork, 0));
     }
+    if (keep.n > 0) HIP_TRY(c, launch_keep_rows(keep, st));
     for (int i : dset) {
         GroupArgs ga = c->pargs.g[(size_t)i];
         ga.samples = resolved[(size_t)i];
@@ -677,17 +711,20 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
             MomentumArgs ma = g.mom_args;
             ma.vel = src[i];
             ma.vec4 = g.d.n_atoms % 4 == 0 && reinterpret_cast<uintptr_t>(src[i]) % 16 == 0;
+            ma.out = made[(size_t)i];
             ma.stamps = pst_stamps;
             HIP_TRY(c, launch_momentum(ma, pst));
         } else if (g.rhok_mfma) {
             RhokMfmaArgs ma = g.margs;
             ma.pos = static_cast<const float *>(src[i]);
+            ma.out = made[(size_t)i];
             ma.stamps = pst_stamps;
             ma.early_loads = fork && !chained ? 1 : 0; // beside the flush, joined every push
             HIP_TRY(c, launch_rhok_mfma(ma, pst));
         } else {
             RhokArgs ra = g.rargs;
             ra.pos = static_cast<const float *>(src[i]);
+            ra.out = made[(size_t)i];
             ra.stamps = pst_stamps;
             HIP_TRY(c, launch_rhok(ra, pst));
         }
@@ -697,8 +734,8 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         // the per-step push of every direct group, sample-fed ones included,
         // in one launch after the producers: the main stream keeps only the
         // staging and the flush of the block-deferred groups
-        std::vector<int> idx(c->main_set);
-        idx.insert(idx.end(), c->side_set.begin(), c->side_set.end());
+        std::vector<int> idx(c->main_upd);
+        idx.insert(idx.end(), c->side_upd.begin(), c->side_upd.end());
         int rc = launch_set(c, c->pa_direct, step_side(c), idx, resolved, pst);
         if (rc != CORR_OK) return rc;
         if (chained) {
@@ -713,14 +750,14 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         }
     } else if (fork) {
         // no flush to overlap: the sample-fed groups run beside the producers
-        int rc = launch_set(c, c->pa_side, step_side(c), c->side_set, resolved, pst);
+        int rc = launch_set(c, c->pa_side, step_side(c), c->side_upd, resolved, pst);
         if (rc != CORR_OK) return rc;
         HIP_TRY(c, hipEventRecord(c->ev_join, pst));
-        rc = launch_set(c, c->pa_main, step_main(c), c->main_set, resolved, st);
+        rc = launch_set(c, c->pa_main, step_main(c), c->main_upd, resolved, st);
         if (rc != CORR_OK) return rc;
     } else {
-        std::vector<int> idx(c->main_set);
-        idx.insert(idx.end(), c->side_set.begin(), c->side_set.end());
+        std::vector<int> idx(c->main_upd);
+        idx.insert(idx.end(), c->side_upd.begin(), c->side_upd.end());
         if (!idx.empty()) {
             hipStream_t ust = st;
             if (fork_updates) {
@@ -745,6 +782,10 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     if (fork_updates) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     if (fork && !chained) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (!c->multi_set.empty() && ++c->waiting == kMultiT) {
+        int rc = add_waiting(c, c->n_push + 1);
+        if (rc != CORR_OK) return rc;
+    }
     if (!c->counted) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
@@ -1241,6 +1282,30 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
         if (g.deferred) c->deferred_set.push_back(i);
         tile_first += g.n_tiles;
     }
+    // Per-step groups whose pushes wait for multi-step passes: not where a
+    // captured graph or the timing takes every push by itself, nor in the
+    // contrast forms; the waiting rows take at most a sixteenth of the free
+    // memory.  The sums are the same bit for bit either way.
+    if (!c->counted && !(flags & (CORR_FLAG_DIRECT | CORR_FLAG_PER_GROUP))) {
+        size_t free_b = 0, total_b = 0, left = 0;
+        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) left = free_b / 16;
+        for (int i = 0; i < n_groups; ++i) {
+            Group &g = c->groups[(size_t)i];
+            if (g.deferred || g.wdef || is_window(c->pargs.g[i]) || !multi_supported(g.kind, g.p, g.m, g.pair))
+                continue;
+            const int64_t row = ((int64_t)(g.pair ? 2 : 1) * g.n_ch * g.s_bytes + 255) / 256 * 256;
+            if ((size_t)row * kMultiT > left) continue;
+            if (hipMalloc(&g.rows, (size_t)row * kMultiT) != hipSuccess) {
+                (void)hipGetLastError();
+                g.rows = nullptr;
+                continue;
+            }
+            left -= (size_t)row * kMultiT;
+            g.row_bytes = row;
+            g.multi = true;
+            c->multi_set.push_back(i);
+        }
+    }
     c->pargs.n_groups = n_groups;
     c->pargs.total_tiles = tile_first;
     c->total_tiles = tile_first;
@@ -1250,11 +1315,13 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
             c->side_set.push_back(i);
         else if (!g.deferred)
             c->main_set.push_back(i);
+        if (g.multi || g.deferred) continue;
+        (g.produced() ? c->side_upd : c->main_upd).push_back(i);
     }
     {
-        std::vector<int> both(c->main_set);
-        both.insert(both.end(), c->side_set.begin(), c->side_set.end());
-        const std::vector<int> *sets[3] = {&c->main_set, &c->side_set, &both};
+        std::vector<int> both(c->main_upd);
+        both.insert(both.end(), c->side_upd.begin(), c->side_upd.end());
+        const std::vector<int> *sets[3] = {&c->main_upd, &c->side_upd, &both};
         PushArgs *pas[3] = {&c->pa_main, &c->pa_side, &c->pa_direct};
         for (int pass = 0; pass < 3; ++pass) {
             const std::vector<int> &idx = *sets[pass];
@@ -1686,6 +1753,10 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
     if (o.gk_kind != 0 && !(o.volume > 0 && o.kB > 0 && o.temperature > 0))
         return set_err(ctx, CORR_E_INVALID, "Green-Kubo prefactor needs volume, kB, temperature > 0");
 
+    {
+        int rc = add_waiting(ctx, ctx->n_push);
+        if (rc != CORR_OK) return rc;
+    }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const int64_t S = ctx->n_push;
     const int tw = ctx->tuning.tile_channels;

@@ -124,3 +124,85 @@ def test_producer_atom_blocks(corrmod, source, atoms):
             got = c.finalize(0, slice_=(0, len(expect)))["c_per_channel"][:, 0]
         err = np.max(np.abs(got - expect)) / np.max(expect)
         assert err < 2e-6, f"{source} atoms={atoms} nk={nk}: {err:.2e}"
+
+
+def _same_readout(a, b, label):
+    for k in ("t", "c", "count", "gk_running", "c_per_channel"):
+        assert np.array_equal(a[k], b[k]), f"{label}: {k} differs"
+
+
+@pytest.mark.parametrize("dtype,accum", [("f32", "kahan"), ("f32", "f64"), ("f32", "f32"), ("f64", "f64"),
+                                         ("cf32", "kahan"), ("cf32", "f64"), ("cf32", "f32"), ("cf64", "f64")])
+@pytest.mark.parametrize("pair", [False, True])
+def test_multi_step_push(corrmod, dtype, accum, pair):
+    """Waiting pushes added in passes of up to 64 against one push at a time
+    (the per-group form): the same bits, for blocks of channels with and without
+    a remainder, readouts at every kind of place in a pass, samples that
+    are not 16-byte aligned and a caller's buffer that changes after each push;
+    autocorrelations also against the oracle."""
+    S, levels = 333, 7
+    stops = (1, 2, 15, 31, 33, 63, 64, 65, 66, 127, 128, 192, 193, 250, 251, 333)
+    for p, n in ((16, 33), (24, 64), (32, 7), (16, 100), (32, 129), (8, 40)):
+        say(f"[multi-step] {dtype}/{accum} pair={pair} p={p} n={n}")
+        x = ou_inputs(5 + p, 1, (2 if pair else 1) * n, S, dtype)
+        xt = torch.from_numpy(x).cuda()
+        cplx = np.iscomplexobj(x)
+        o = oracle.OracleCorrelator(n, levels, p, 2, complex_=cplx)
+        g = corrmod.GroupDesc(n, levels, p, 2, dtype=dtype, accum=accum, pair=pair)
+        buf = torch.empty(xt.shape[1] + 1, dtype=xt.dtype, device="cuda")[1:]
+        with corrmod.Correlator([g]) as c, corrmod.Correlator([g], per_group=True) as ref:
+            s = 0
+            for stop in stops:
+                while s < stop:
+                    buf.copy_(xt[s])
+                    c.push([buf])
+                    ref.push([xt[s]])
+                    if not pair:
+                        o.push(x[s].astype(np.complex128 if cplx else np.float64))
+                    s += 1
+                r = c.finalize(0, slice_=(0, n))
+                if not (dtype == "f32" and p == 16 and not pair):  # (that one is block-deferred)
+                    _same_readout(r, ref.finalize(0, slice_=(0, n)), f"p={p} n={n} S={s}")
+                if not pair:  # (a pair's C(0) is no scale of its errors)
+                    _check_channels(r, o, [(i, i) for i in (0, n // 2, n - 1)], TOL[(dtype, accum)], f"S={s}")
+
+
+def test_multi_step_push_of_producers(corrmod):
+    """Producers that write their waiting row, a momentum pair group and sample
+    groups in one context, with the producers beside the other groups and on
+    one stream: bit-identical to the per-group form."""
+    N, nk, box, S = 700, 37, 30.0, 150
+    kv = synth.kvectors(nk)
+    rng = np.random.default_rng(4)
+    pos = rng.uniform(0, box, (S, 3, N)).astype(np.float32)
+    vel = rng.standard_normal((S, 3, N)).astype(np.float32)
+    q = rng.standard_normal((S, 3)).astype(np.float32)
+    both = np.concatenate([pos, vel], 1).reshape(S, -1)
+    mom = np.concatenate([vel.reshape(S, -1), q, q], 1)
+    st = rng.standard_normal((S, 9))
+    inputs = [torch.from_numpy(np.ascontiguousarray(a)).cuda()
+              for a in (pos.reshape(S, -1), both, mom, st, q)]
+    kw = dict(dtype="cf32", accum="kahan", kvec=kv, n_atoms=N, box=box)
+    groups = [corrmod.GroupDesc(nk, 6, 32, 2, source="rhok", **kw),
+              corrmod.GroupDesc(3 * nk, 6, 16, 2, source="currents", **kw),
+              corrmod.GroupDesc(6, 6, 16, 2, dtype="f32", accum="kahan", source="momentum", n_atoms=N, box=box,
+                                species=rng.integers(0, 2, N).astype(np.int32), masses=np.array([2.0, 3.0]),
+                                pair=True),
+              corrmod.GroupDesc(9, 8, 16, 2, dtype="f64", accum="f64"),
+              corrmod.GroupDesc(3, 6, 16, 2, dtype="f32", accum="kahan")]
+    with corrmod.Correlator(groups[:4], per_group=True) as ref:
+        for s in range(S):
+            ref.push([t[s] for t in inputs[:4]])
+        want = [ref.finalize(i, slice_=(0, groups[i].n_channels)) for i in range(4)]
+    for k in (4, 5):
+        for overlap in (0, 1, 2):
+            say(f"[multi-step producers] groups={k} overlap={overlap}")
+            tuning = dict(tile_channels=256, chans_per_thread=2, lag_chunk=8, grid_blocks=0,
+                          overlap_producers=overlap)
+            with corrmod.Correlator(groups[:k], tuning=tuning) as c:
+                for s in range(S):
+                    c.push([t[s] for t in inputs[:k]])
+                    if s in (0, 70):
+                        c.finalize(1)
+                for i in range(4):
+                    _same_readout(c.finalize(i, slice_=(0, groups[i].n_channels)), want[i], f"group {i}")
