@@ -331,23 +331,16 @@ class Correlator:
         if slice_ is not None:
             o.slice_begin, o.slice_end = int(slice_[0]), int(slice_[1])
             ns = o.slice_end - o.slice_begin
-            per = np.zeros((ns, nmax, 2) if cplx else (ns, nmax))
+            per = np.empty((ns, nmax, 2) if cplx else (ns, nmax))
         P = lambda a: None if a is None else a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
         fn = lib().corr_finalize_noalloc if noalloc else lib().corr_finalize
         self._check(fn(self._h, g, ctypes.byref(o), ctypes.byref(n_out), P(t), P(c), P(cnt),
                        P(run), ctypes.byref(at), P(per)))
         n = int(n_out.value)
         res = {"t": t[:n], "count": cnt[:n], "gk_running": run[:n], "gk_at_cut": float(at.value)}
-        if cplx:
-            res["c"] = c[:n, 0] + 1j * c[:n, 1]
-        else:
-            res["c"] = c[:n]
+        res["c"] = c[:n].view(np.complex128)[:, 0] if cplx else c[:n]
         if per is not None:
-            # the library writes [slice][n_out] (complex: [slice][n_out][2]) contiguously
-            ns = per.shape[0]
-            if cplx:
-                flat = per.reshape(-1)[: ns * n * 2].reshape(ns, n, 2)
-                res["c_per_channel"] = flat[:, :, 0] + 1j * flat[:, :, 1]
-            else:
-                res["c_per_channel"] = per.reshape(-1)[: ns * n].reshape(ns, n)
+            # the library writes [slice][n_out] (complex: re, im pairs) contiguously
+            flat = per.reshape(-1).view(np.complex128) if cplx else per.reshape(-1)
+            res["c_per_channel"] = flat[: ns * n].reshape(ns, n)
         return res

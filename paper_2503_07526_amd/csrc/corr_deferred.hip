@@ -249,7 +249,8 @@ __device__ __forceinline__ void fold_level(Ctx &cx, int k, const typename RK<K>:
         if (in_slice) {
 #pragma unroll
             for (int j = 0; j < NL; ++j)
-                if (l0 + j < hi_lag) a.slice_out[(size_t)(cx.ch - a.slice_begin) * a.ne + e0 + j] = v[j];
+                if (l0 + j < hi_lag) // the correlation function: divided by the lag's count
+                    a.slice_out[(size_t)(cx.ch - a.slice_begin) * a.ne + e0 + j] = v[j] / (double)(sk - (l0 + j));
         }
         // Fixed-order sums over the wave's 64 consecutive channels (a chunk
         // aligned to 64 whatever the tile width).

@@ -314,25 +314,37 @@ struct PushEndArgs {
     int32_t n_stamps;                  // records reduced from stamps (1 or 2)
 };
 
-// Readout reduction arguments.
+constexpr int kMaxLevels = 40;
+
+// Readout reduction arguments.  Entry e is a (level, lag) pair with a count,
+// level-major; entries level_e[k] .. level_e[k + 1] - 1 are those of level k.
 struct ReduceArgs {
     const char *state;
     int64_t tile_bytes;
     int32_t tw;
     int32_t kind;
-    const int64_t *hi_off;  // [n_entries] byte offset inside a tile of the entry's row
-    const int64_t *lo_off;  // [n_entries] compensation row offset (compensated kinds)
+    int32_t n_levels;       // levels with entries
+    int32_t lag0;           // first lag of levels >= 1
+    int32_t level_e[kMaxLevels];
+    int64_t level_n[kMaxLevels]; // values that the level has received
+    int64_t lvl0_bytes, lvlk_bytes;
+    int64_t acc0, acck;     // bytes from the start of level 0 (a coarser level) to its accumulator rows
+    int64_t lo0, lok;       // and from a row to its compensation row
+    int64_t row_bytes;      // of an accumulator row
     int32_t n_entries;
     int32_t blocks_per_entry;
     int64_t ch_begin, ch_end;
     double *partial;        // [n_entries][blocks_per_entry][2]
-    double *out;            // [n_entries][2]
+    double *out;            // [n_entries][2] sums; gather: the slice
     // One-level window in the block-deferred form (wlpb > 0): entry e is lag
     // e, lag block e / wlpb; the pushes it has not folded are added from the
     // level-0 ring of p0 rows.
     int32_t wlpb;
     int32_t p0;
     int64_t n_push;         // pushes completed
+    double norm;            // gather: sums divided by the count, times norm
+    int32_t cplx;           // gather: 1: (re, im) pairs written, else re
+    int32_t pad_;
 };
 
 } // namespace corr

@@ -51,7 +51,24 @@ __device__ double2 window_pending(const ReduceArgs &a, int e, int64_t c)
     return make_double2(re, im);
 }
 
-__device__ __forceinline__ double2 stored_acc(const ReduceArgs &a, int e, int64_t c)
+// Where entry e's accumulators lie inside a tile, and its count.
+struct EntryRow {
+    int64_t hi, lo, count;
+};
+
+__device__ __forceinline__ EntryRow entry_row(const ReduceArgs &a, int e)
+{
+    int k = 0;
+    while (k + 1 < a.n_levels && e >= a.level_e[k + 1]) ++k;
+    const int j = e - a.level_e[k];
+    EntryRow r;
+    r.hi = (k == 0 ? a.acc0 : a.lvl0_bytes + (int64_t)(k - 1) * a.lvlk_bytes + a.acck) + j * a.row_bytes;
+    r.lo = r.hi + (k == 0 ? a.lo0 : a.lok);
+    r.count = a.level_n[k] - (k == 0 ? 0 : a.lag0) - j;
+    return r;
+}
+
+__device__ __forceinline__ double2 stored_acc(const ReduceArgs &a, const EntryRow &r, int64_t c)
 {
     const int64_t tile = c / a.tw;
     const int64_t lane = c - tile * a.tw;
@@ -59,32 +76,32 @@ __device__ __forceinline__ double2 stored_acc(const ReduceArgs &a, int e, int64_
     switch (a.kind) {
     case K_F32_F64:
     case K_F64_F64:
-        return make_double2(reinterpret_cast<const double *>(tb + a.hi_off[e])[lane], 0.0);
+        return make_double2(reinterpret_cast<const double *>(tb + r.hi)[lane], 0.0);
     case K_F32_KAHAN: {
-        const float h = reinterpret_cast<const float *>(tb + a.hi_off[e])[lane];
-        const float l = reinterpret_cast<const float *>(tb + a.lo_off[e])[lane];
+        const float h = reinterpret_cast<const float *>(tb + r.hi)[lane];
+        const float l = reinterpret_cast<const float *>(tb + r.lo)[lane];
         return make_double2((double)h - (double)l, 0.0);
     }
     case K_F32_F32:
-        return make_double2((double)reinterpret_cast<const float *>(tb + a.hi_off[e])[lane], 0.0);
+        return make_double2((double)reinterpret_cast<const float *>(tb + r.hi)[lane], 0.0);
     case K_CF32_F64:
     case K_CF64_F64:
-        return reinterpret_cast<const double2 *>(tb + a.hi_off[e])[lane];
+        return reinterpret_cast<const double2 *>(tb + r.hi)[lane];
     case K_CF32_KAHAN: {
-        const float2 h = reinterpret_cast<const float2 *>(tb + a.hi_off[e])[lane];
-        const float2 l = reinterpret_cast<const float2 *>(tb + a.lo_off[e])[lane];
+        const float2 h = reinterpret_cast<const float2 *>(tb + r.hi)[lane];
+        const float2 l = reinterpret_cast<const float2 *>(tb + r.lo)[lane];
         return make_double2((double)h.x - (double)l.x, (double)h.y - (double)l.y);
     }
     default: {
-        const float2 h = reinterpret_cast<const float2 *>(tb + a.hi_off[e])[lane];
+        const float2 h = reinterpret_cast<const float2 *>(tb + r.hi)[lane];
         return make_double2((double)h.x, (double)h.y);
     }
     }
 }
 
-__device__ __forceinline__ double2 read_acc(const ReduceArgs &a, int e, int64_t c)
+__device__ __forceinline__ double2 read_acc(const ReduceArgs &a, int e, const EntryRow &r, int64_t c)
 {
-    double2 v = stored_acc(a, e, c);
+    double2 v = stored_acc(a, r, c);
     if (a.wlpb > 0) {
         const double2 w = window_pending(a, e, c);
         v.x += w.x;
@@ -106,8 +123,9 @@ __global__ __launch_bounds__(kRedThreads) void reduce_partial_kernel(ReduceArgs 
     int64_t b1 = b0 + per;
     if (b1 > a.ch_end) b1 = a.ch_end;
     double ar = 0.0, ai = 0.0;
+    const EntryRow row = entry_row(a, e);
     for (int64_t c = b0 + threadIdx.x; c < b1; c += kRedThreads) {
-        const double2 v = read_acc(a, e, c);
+        const double2 v = read_acc(a, e, row, c);
         ar += v.x;
         ai += v.y;
     }
@@ -141,7 +159,12 @@ __global__ void reduce_final_kernel(ReduceArgs a)
     a.out[2 * e + 1] = i;
 }
 
-// out[(c - ch_begin) * n_entries + e][2] for c in [ch_begin, ch_end).
+// Correlation functions of the channels [ch_begin, ch_end) as the caller takes
+// them, out[(c - ch_begin) * n_entries + e] (complex: re, im): the division by
+// the count is done here, and the result copied straight into the caller's
+// array (the division by the host, on zero-filled copies, and the binding's
+// complex arithmetic made a readout of a slice of 6144 channels and 59 entries
+// take 1.7 ms; now 0.7, nearly all of it the copy into fresh host pages).
 __global__ void gather_kernel(ReduceArgs a)
 {
     const int64_t n = (a.ch_end - a.ch_begin) * a.n_entries;
@@ -149,9 +172,13 @@ __global__ void gather_kernel(ReduceArgs a)
          i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t c = a.ch_begin + i / a.n_entries;
         const int e = (int)(i % a.n_entries);
-        const double2 v = read_acc(a, e, c);
-        a.out[2 * i + 0] = v.x;
-        a.out[2 * i + 1] = v.y;
+        const EntryRow row = entry_row(a, e);
+        const double2 v = read_acc(a, e, row, c);
+        const double den = (double)row.count;
+        if (a.cplx)
+            reinterpret_cast<double2 *>(a.out)[i] = make_double2(v.x / den * a.norm, v.y / den * a.norm);
+        else
+            a.out[i] = v.x / den * a.norm;
     }
 }
 

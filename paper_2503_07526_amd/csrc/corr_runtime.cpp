@@ -58,6 +58,9 @@ hipError_t noalloc_scratch(int device, void **out)
 // (kWindowLags lags per block).
 constexpr int kWindowMinP = 512;
 constexpr int kWindowLags = 256;
+// Pinned host memory of a context: the sums of the longest window (16384
+// complex entries) and, beside shorter ones, slices up to this size.
+constexpr size_t kPinnedBytes = (size_t)320 << 10;
 
 struct Group {
     corr_group_desc d{};
@@ -173,6 +176,8 @@ struct corr_ctx {
     size_t scratch_bytes = 0;
     // this device's fixed readout scratch (corr_finalize_noalloc)
     void *noalloc = nullptr;
+    // host memory that the readout kernels write their sums and small slices to
+    char *pinned = nullptr;
     std::string err;
 };
 
@@ -295,7 +300,8 @@ int validate(const corr_group_desc &g, int idx)
         }
     }
     if (g.points > 16384) return set_err(nullptr, CORR_E_UNSUPPORTED, "group %d: p > 16384", idx);
-    if (g.levels > 40) return set_err(nullptr, CORR_E_UNSUPPORTED, "group %d: b > 40", idx);
+    if (g.levels > kMaxLevels)
+        return set_err(nullptr, CORR_E_UNSUPPORTED, "group %d: b > %d", idx, kMaxLevels);
     return CORR_OK;
 }
 
@@ -359,6 +365,7 @@ void free_ctx(corr_ctx *c)
     if (c->d_step) (void)hipFree(c->d_step);
     if (c->d_stamps) (void)hipFree(c->d_stamps);
     if (c->d_scratch) (void)hipFree(c->d_scratch);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     for (auto &pl : c->pools) {
         for (auto e : pl.start) (void)hipEventDestroy(e);
         for (auto e : pl.end) (void)hipEventDestroy(e);
@@ -849,7 +856,6 @@ int ensure_scratch(corr_ctx *c, size_t bytes)
 struct Entry {
     int level, lag;
     int64_t count;
-    int64_t hi_off, lo_off;
 };
 
 } // namespace
@@ -1348,6 +1354,7 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
     CREATE_HIP(hipMemsetAsync(c->d_step, 0, 2 * sizeof(int64_t), c->stream));
     c->d_step_side = c->d_step + 1;
     CREATE_HIP(noalloc_scratch(device, &c->noalloc));
+    CREATE_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->pinned), kPinnedBytes, hipHostMallocDefault));
     if (flags & CORR_FLAG_TIMING) {
         int khz = 0;
         CREATE_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device));
@@ -1757,7 +1764,6 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         int rc = add_waiting(ctx, ctx->n_push);
         if (rc != CORR_OK) return rc;
     }
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const int64_t S = ctx->n_push;
     const int tw = ctx->tuning.tile_channels;
     const int64_t rowS = (int64_t)tw * g.s_bytes;
@@ -1769,8 +1775,6 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         int64_t Sk = S;
         for (int k = 0; k < g.b && Sk > 0; ++k) {
             const int l0 = k == 0 ? 0 : g.lag0;
-            const int nl = k == 0 ? g.p : g.nlk;
-            const int64_t lvl = k == 0 ? 0 : g.lvl0_bytes + (int64_t)(k - 1) * g.lvlk_bytes;
             for (int L = l0; L < g.p; ++L) {
                 const int64_t cnt = Sk - L;
                 if (cnt <= 0) continue;
@@ -1778,9 +1782,6 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
                 e.level = k;
                 e.lag = L;
                 e.count = cnt;
-                const int ring_rows = (g.pair ? 2 : 1) * (k == 0 ? g.p0 : g.p);
-                e.hi_off = lvl + (int64_t)ring_rows * rowS + (int64_t)(L - l0) * rowA;
-                e.lo_off = e.hi_off + (int64_t)nl * rowA;
                 ent.push_back(e);
             }
             Sk /= g.m;
@@ -1796,7 +1797,9 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
     const int bpe = (int)std::max<int64_t>(1, std::min<int64_t>(256, (nsel + 4095) / 4096));
     const int64_t n_slice = want_slice ? (se - sb) : 0;
     std::vector<double> sums((size_t)ne * 2);
-    std::vector<double> slice;
+    const bool cplx = kind_complex(g.kind);
+    // F(k,t) = <n n*> / N; currents likewise per atom
+    const double norm = g.rhok ? 1.0 / (double)g.d.n_atoms : 1.0;
     if (g.deferred) {
         // Block-deferred group: fold pending complete blocks (the scheduled
         // flush would produce the same state), then fold the pushes after the
@@ -1812,7 +1815,7 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         const size_t gr_bytes = round256((size_t)n_cg * ne * sizeof(double));
         const size_t s_bytes = round256((size_t)ne * sizeof(double));
         const size_t sl_bytes = round256((size_t)std::max<int64_t>(n_slice, 1) * ne * sizeof(double));
-        const size_t fixed = gr_bytes + s_bytes + sl_bytes;
+        const size_t fixed = gr_bytes + sl_bytes;
         const size_t cg_bytes = (size_t)cg_rows * ne * sizeof(double);
         int64_t cg_per_pass = n_cg;
         if (noalloc) {
@@ -1842,63 +1845,67 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         da.slice_end = want_slice ? se : 0;
         da.chunk_partial = reinterpret_cast<double *>(sc);
         double *d_groups = reinterpret_cast<double *>(sc + tp_bytes);
-        double *d_sums = reinterpret_cast<double *>(sc + tp_bytes + gr_bytes);
-        da.slice_out = reinterpret_cast<double *>(sc + tp_bytes + gr_bytes + s_bytes);
+        da.slice_out = reinterpret_cast<double *>(sc + tp_bytes + gr_bytes);
         for (int64_t g0 = 0; g0 < n_cg; g0 += cg_per_pass) {
             const int64_t g1 = std::min(n_cg, g0 + cg_per_pass);
             da.row_begin = g0 * cg_rows;
             da.row_end = std::min(n_rows, g1 * cg_rows);
             HIP_TRY(ctx, launch_deferred_readout_pass(da, d_groups, ctx->stream));
         }
-        HIP_TRY(ctx, launch_deferred_readout_final(da, d_groups, d_sums, ctx->stream));
-        std::vector<double> re((size_t)ne);
-        HIP_TRY(ctx, hipMemcpyAsync(re.data(), d_sums, (size_t)ne * sizeof(double),
-                                    hipMemcpyDeviceToHost, ctx->stream));
-        std::vector<double> sl;
-        if (want_slice) {
-            sl.resize((size_t)n_slice * ne);
-            HIP_TRY(ctx, hipMemcpyAsync(sl.data(), da.slice_out, (size_t)n_slice * ne * sizeof(double),
-                                        hipMemcpyDeviceToHost, ctx->stream));
-        }
+        // (the sums are written to the pinned buffer by the kernel; a block-deferred
+        // group has at most 16 + 39 x 8 entries)
+        const size_t slice_bytes = (size_t)n_slice * ne * sizeof(double);
+        const bool pin_slice = s_bytes + slice_bytes <= kPinnedBytes;
+        double *const re = reinterpret_cast<double *>(ctx->pinned);
+        HIP_TRY(ctx, launch_deferred_readout_final(da, d_groups, re, ctx->stream));
+        if (want_slice)
+            HIP_TRY(ctx, hipMemcpyAsync(pin_slice ? static_cast<void *>(ctx->pinned + s_bytes) : c_per_channel,
+                                        da.slice_out, slice_bytes, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         for (int i = 0; i < ne; ++i) {
-            sums[(size_t)2 * i] = re[(size_t)i];
+            sums[(size_t)2 * i] = re[i];
             sums[(size_t)2 * i + 1] = 0.0;
         }
-        if (want_slice) {
-            slice.assign((size_t)n_slice * ne * 2, 0.0);
-            for (size_t i = 0; i < sl.size(); ++i) slice[2 * i] = sl[i];
-        }
+        if (want_slice && pin_slice) std::memcpy(c_per_channel, ctx->pinned + s_bytes, slice_bytes);
     } else {
-    // scratch: offsets (2 * ne int64), partial (ne * bpe * 2 doubles), sums (ne * 2 doubles),
-    // slice (n_slice * ne * 2 doubles)
-    const size_t off_bytes = (size_t)2 * ne * sizeof(int64_t);
+    // scratch: partial (ne * bpe * 2 doubles) and, where the pinned buffer does not hold them,
+    // sums (ne * 2 doubles) and slice (n_slice * ne doubles or pairs)
     const size_t part_bytes = (size_t)ne * bpe * 2 * sizeof(double);
     const size_t sum_bytes = (size_t)ne * 2 * sizeof(double);
-    const size_t slice_bytes = (size_t)n_slice * ne * 2 * sizeof(double);
-    const size_t total = off_bytes + part_bytes + sum_bytes + std::max(slice_bytes, (size_t)16);
+    const size_t slice_bytes = (size_t)n_slice * ne * (cplx ? 2 : 1) * sizeof(double);
+    // The sums, and a slice that fits behind them, are written to the pinned
+    // buffer by the kernels themselves.
+    const bool pin_sums = sum_bytes <= kPinnedBytes;
+    const bool pin_slice = pin_sums && sum_bytes + slice_bytes <= kPinnedBytes;
     char *sc = nullptr;
     {
-        int rc = readout_scratch(ctx, noalloc, total, &sc);
+        int rc = readout_scratch(ctx, noalloc, part_bytes + (pin_sums ? 0 : sum_bytes) + (pin_slice ? 0 : slice_bytes), &sc);
         if (rc != CORR_OK) return rc;
     }
-    int64_t *d_off = reinterpret_cast<int64_t *>(sc);
-    double *d_part = reinterpret_cast<double *>(sc + off_bytes);
-    double *d_sum = reinterpret_cast<double *>(sc + off_bytes + part_bytes);
-    double *d_slice = reinterpret_cast<double *>(sc + off_bytes + part_bytes + sum_bytes);
-    std::vector<int64_t> offs((size_t)2 * ne);
-    for (int i = 0; i < ne; ++i) {
-        offs[(size_t)i] = ent[(size_t)i].hi_off;
-        offs[(size_t)ne + i] = ent[(size_t)i].lo_off;
-    }
-    HIP_TRY(ctx, hipMemcpyAsync(d_off, offs.data(), off_bytes, hipMemcpyHostToDevice, ctx->stream));
+    double *d_part = reinterpret_cast<double *>(sc);
+    double *d_sum = reinterpret_cast<double *>(pin_sums ? ctx->pinned : sc + part_bytes);
+    double *d_slice = reinterpret_cast<double *>(pin_slice ? ctx->pinned + sum_bytes
+                                                           : sc + part_bytes + (pin_sums ? 0 : sum_bytes));
     ReduceArgs ra{};
     ra.state = g.state;
     ra.tile_bytes = g.tile_bytes;
     ra.tw = tw;
     ra.kind = g.kind;
-    ra.hi_off = d_off;
-    ra.lo_off = d_off + ne;
+    for (int i = 0; i < ne; ++i) {
+        const Entry &e = ent[(size_t)i];
+        if (e.level + 1 == ra.n_levels) continue;
+        ra.level_e[e.level] = i; // its first entry
+        ra.level_n[e.level] = e.count + e.lag;
+        ra.n_levels = e.level + 1;
+    }
+    ra.lag0 = g.lag0;
+    ra.lvl0_bytes = g.lvl0_bytes;
+    ra.lvlk_bytes = g.lvlk_bytes;
+    ra.acc0 = (int64_t)(g.pair ? 2 : 1) * g.p0 * rowS;
+    ra.acck = (int64_t)(g.pair ? 2 : 1) * g.p * rowS;
+    ra.lo0 = (int64_t)g.p * rowA;
+    ra.lok = (int64_t)g.nlk * rowA;
+    ra.row_bytes = rowA;
     ra.n_entries = ne;
     ra.blocks_per_entry = bpe;
     ra.ch_begin = cb;
@@ -1909,23 +1916,25 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
     ra.p0 = g.p0;
     ra.n_push = S;
     HIP_TRY(ctx, launch_reduce(ra, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(sums.data(), d_sum, sum_bytes, hipMemcpyDeviceToHost, ctx->stream));
+    if (!pin_sums)
+        HIP_TRY(ctx, hipMemcpyAsync(sums.data(), d_sum, sum_bytes, hipMemcpyDeviceToHost, ctx->stream));
     if (want_slice) {
         ReduceArgs rs = ra;
         rs.ch_begin = sb;
         rs.ch_end = se;
         rs.out = d_slice;
+        rs.norm = norm;
+        rs.cplx = cplx ? 1 : 0;
         HIP_TRY(ctx, launch_gather(rs, ctx->stream));
-        slice.resize((size_t)n_slice * ne * 2);
-        HIP_TRY(ctx, hipMemcpyAsync(slice.data(), d_slice, slice_bytes, hipMemcpyDeviceToHost,
-                                    ctx->stream));
+        if (!pin_slice)
+            HIP_TRY(ctx, hipMemcpyAsync(c_per_channel, d_slice, slice_bytes, hipMemcpyDeviceToHost,
+                                        ctx->stream));
     }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    if (pin_sums) std::memcpy(sums.data(), ctx->pinned, sum_bytes);
+    if (want_slice && pin_slice) std::memcpy(c_per_channel, ctx->pinned + sum_bytes, slice_bytes);
     }
 
-    const bool cplx = kind_complex(g.kind);
-    // F(k,t) = <n n*> / N; currents likewise per atom
-    const double norm = g.rhok ? 1.0 / (double)g.d.n_atoms : 1.0;
     const double tunit = (double)g.d.update_every * g.d.dt;
     std::vector<double> tt((size_t)ne), cre((size_t)ne);
     for (int i = 0; i < ne; ++i) {
@@ -1945,20 +1954,6 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         } else {
             c[i] = vr;
         }
-    }
-    if (want_slice) {
-        for (int64_t s = 0; s < n_slice; ++s)
-            for (int i = 0; i < ne; ++i) {
-                const double den = (double)ent[(size_t)i].count;
-                const double vr = slice[((size_t)s * ne + i) * 2] / den * norm;
-                const double vi = slice[((size_t)s * ne + i) * 2 + 1] / den * norm;
-                if (cplx) {
-                    c_per_channel[((size_t)s * ne + i) * 2] = vr;
-                    c_per_channel[((size_t)s * ne + i) * 2 + 1] = vi;
-                } else {
-                    c_per_channel[(size_t)s * ne + i] = vr;
-                }
-            }
     }
     // Green-Kubo: trapezoid of Re C over the emitted lag grid from t = 0 (the
     // grid is increasing when m divides p; otherwise it is taken in sorted order).
