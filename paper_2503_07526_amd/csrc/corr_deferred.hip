@@ -765,6 +765,44 @@ __global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, i
     }
 }
 
+// The staging of n_rows consecutive pushes (push r's samples `pitch` bytes after
+// push r - 1's): each thread moves 4 channels of kStageUnroll rows, whose ring
+// rows are neighbours in the tile; blockIdx.y counts the row quads.
+// 244 pushes of 900000 channels take 321 us (5.5 TB/s) instead of 4.4 us each
+// (1.6 TB/s) as launches of their own.
+__global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef step, int64_t pitch,
+                                                          int n_rows, int aligned)
+{
+    const int r0 = (int)blockIdx.y * kStageUnroll;
+    const int slot0 = (int)((pushes_before(step) + r0) % g.p0);
+    const int64_t n = g.n_ch;
+    const int64_t nvec = (n + kStageVec - 1) / kStageVec;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
+        const int64_t c = v * kStageVec;
+        const int64_t tile = c / g.tw;
+        const int64_t lane = c - tile * g.tw;
+        float *ring = reinterpret_cast<float *>(g.state + tile * g.tile_bytes) + lane;
+        stage_f4 x[kStageUnroll];
+#pragma unroll
+        for (int u = 0; u < kStageUnroll; ++u) {
+            if (r0 + u >= n_rows) continue;
+            const float *src = reinterpret_cast<const float *>(static_cast<const char *>(g.samples) + (r0 + u) * pitch);
+            if (aligned && c + kStageVec <= n)
+                x[u] = __builtin_nontemporal_load(reinterpret_cast<const stage_f4 *>(src + c));
+            else
+                for (int i = 0; i < kStageVec; ++i) x[u][i] = c + i < n ? src[c + i] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kStageUnroll; ++u) {
+            if (r0 + u >= n_rows) continue;
+            int slot = slot0 + u;
+            if (slot >= g.p0) slot -= g.p0;
+            __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(ring + (size_t)slot * g.tw));
+        }
+    }
+}
+
 } // namespace
 
 hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st)
@@ -776,6 +814,19 @@ hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st)
     int64_t blocks = (nvec + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g, step, aligned);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_rows(const GroupArgs &g, StepRef step, int64_t pitch, int n_rows, hipStream_t st)
+{
+    if (n_rows < 1 || n_rows > g.p0) return hipErrorInvalidValue;
+    const int aligned = ((uintptr_t)g.samples % 16) == 0 && pitch % 16 == 0;
+    const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
+    int64_t blocks = (nvec + 255) / 256;
+    if (blocks > 2048) blocks = 2048;
+    const unsigned quads = (unsigned)((n_rows + kStageUnroll - 1) / kStageUnroll);
+    hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)blocks, quads), dim3(256), 0, st, g, step, pitch,
+                       n_rows, aligned);
     return hipGetLastError();
 }
 

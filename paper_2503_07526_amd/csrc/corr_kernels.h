@@ -37,6 +37,8 @@ int rhok_mfma_blocks_per_cu(int n_mtiles, int nw, int table_rows); // blocks tha
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st);
 bool deferred_supported(int kind, int p, int m);
 hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st);
+// n_rows (at most p0) consecutive pushes, push r at g.samples + r pitch
+hipError_t launch_stage_rows(const GroupArgs &g, StepRef step, int64_t pitch, int n_rows, hipStream_t st);
 hipError_t launch_flush_fold(const DeferredArgs &a, hipStream_t st);   // the fold kernel
 // Fold of block a.fixed_block for every tile group (a.fixed_group == -2) with
 // level 0 read from the history a.hist (a.hist_stride bytes per push).

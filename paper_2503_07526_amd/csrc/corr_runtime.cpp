@@ -491,28 +491,36 @@ int commit_block(corr_ctx *c, const std::vector<int> &idx, int64_t q, int32_t ad
     return CORR_OK;
 }
 
-// Fold block q of the groups idx in every tile group that has not folded it
-// yet (one launch for each run of such tile groups: the scheduled folds go
-// through them in order, so there is one run), and record it.
+// Fold block q of group i in those of its tile groups [j0, j1) that have not
+// folded it yet: one launch for each run of them (the scheduled folds go
+// through them in order, so there is one run).
+int fold_range(corr_ctx *c, int i, int64_t q, int j0, int j1)
+{
+    const Group &g = c->groups[(size_t)i];
+    for (int j = j0; j < j1;) {
+        if (g.flushed[(size_t)j] >= q) {
+            ++j;
+            continue;
+        }
+        int e = j;
+        while (e < j1 && g.flushed[(size_t)e] < q) ++e;
+        DeferredArgs da = deferred_args(c, i);
+        da.fixed_group = -2;
+        da.fixed_block = q;
+        da.tile_first = std::min(g.n_tiles, j * g.tiles_per_group);
+        da.tile_end = std::min(g.n_tiles, e * g.tiles_per_group);
+        if (da.tile_end > da.tile_first) HIP_TRY(c, launch_flush_fold(da, c->stream));
+        j = e;
+    }
+    return CORR_OK;
+}
+
+// Fold block q of the groups idx in every tile group and record it.
 int fold_all(corr_ctx *c, const std::vector<int> &idx, int64_t q)
 {
     for (int i : idx) {
-        const Group &g = c->groups[(size_t)i];
-        for (int j = 0; j < g.T;) {
-            if (g.flushed[(size_t)j] >= q) {
-                ++j;
-                continue;
-            }
-            int j1 = j;
-            while (j1 < g.T && g.flushed[(size_t)j1] < q) ++j1;
-            DeferredArgs da = deferred_args(c, i);
-            da.fixed_group = -2;
-            da.fixed_block = q;
-            da.tile_first = std::min(g.n_tiles, j * g.tiles_per_group);
-            da.tile_end = std::min(g.n_tiles, j1 * g.tiles_per_group);
-            if (da.tile_end > da.tile_first) HIP_TRY(c, launch_flush_fold(da, c->stream));
-            j = j1;
-        }
+        int rc = fold_range(c, i, q, 0, c->groups[(size_t)i].T);
+        if (rc != CORR_OK) return rc;
     }
     return commit_block(c, idx, q, 0, false);
 }
@@ -1551,14 +1559,76 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
         return CORR_OK;
     }
 
+    // The pushes of rows [r0, r0 + n) for the groups that are not
+    // block-deferred.  Sample groups with multi-step passes take them from the
+    // history when no other group needs a launch for every push.
+    const bool each_push = ctx->counted || !ctx->side_set.empty() || !ctx->main_upd.empty();
+    auto other_pushes = [&](int32_t r0, int32_t n) -> int {
+        if (!each_push) {
+            int rc = add_waiting(ctx, ctx->n_push);
+            if (rc != CORR_OK) return rc;
+            for (int i : ctx->multi_set)
+                for (int32_t k = 0; k < n; k += kMultiT)
+                    HIP_TRY(ctx, launch_multi_push(ctx->pargs.g[i], StepRef{nullptr, ctx->n_push + k},
+                                                   static_cast<const char *>(samples[i]) + (int64_t)(r0 + k) * stride[(size_t)i],
+                                                   stride[(size_t)i], std::min(kMultiT, n - k), ctx->stream));
+            ctx->n_push += n;
+            return CORR_OK;
+        }
+        for (int32_t k = 0; k < n; ++k) {
+            row(r0 + k);
+            int rc = issue_push(ctx, src.data(), ctx->stream, false, true);
+            if (rc != CORR_OK) return rc;
+            ctx->n_push += 1;
+        }
+        return CORR_OK;
+    };
+    // The pushes of rows [r0, r0 + n) for every group, up to the next multiple
+    // of T at most if there are block-deferred groups (the ring then still holds
+    // what the folds not done yet read): those stage all n rows in one launch,
+    // then fold what was scheduled for these pushes.
+    auto some_pushes = [&](int32_t r0, int32_t n) -> int {
+        if (ctx->counted) {
+            for (int32_t k = 0; k < n; ++k) {
+                int rc = one_push(r0 + k);
+                if (rc != CORR_OK) return rc;
+            }
+            return CORR_OK;
+        }
+        const int64_t S = ctx->n_push;
+        for (int i : ctx->deferred_set) {
+            GroupArgs ga = ctx->pargs.g[i];
+            ga.samples = static_cast<const char *>(samples[i]) + (int64_t)r0 * stride[(size_t)i];
+            HIP_TRY(ctx, launch_stage_rows(ga, StepRef{nullptr, S}, stride[(size_t)i], n, ctx->stream));
+        }
+        int rc = other_pushes(r0, n);
+        if (rc != CORR_OK) return rc;
+        // push s folds block s / T of tile group s % T
+        for (int i : ctx->deferred_set) {
+            Group &g = ctx->groups[(size_t)i];
+            for (int64_t s = S + 1; s <= S + n;) {
+                const int64_t q = s / g.T, e = std::min(S + n + 1, (q + 1) * g.T);
+                const int j0 = (int)(s - q * g.T), j1 = (int)(e - q * g.T);
+                if (q >= 1) {
+                    rc = fold_range(ctx, i, q, j0, j1);
+                    if (rc != CORR_OK) return rc;
+                    for (int j = j0; j < j1; ++j) g.flushed[(size_t)j] = std::max(g.flushed[(size_t)j], q);
+                }
+                s = e;
+            }
+        }
+        return CORR_OK;
+    };
     int32_t r = 0;
     const int T = ctx->defer_t;
     if (!ctx->deferred_set.empty() && n_steps >= T) {
         // Block-deferred groups fold whole blocks of the history directly.
-        // Up to the next block boundary the pushes are single pushes.
-        while (r < n_steps && ctx->n_push % T != 0) {
-            int rc = one_push(r++);
+        // Up to the next block boundary the pushes are staged.
+        if (ctx->n_push % T != 0) {
+            const int32_t n = (int32_t)std::min<int64_t>(n_steps, T - ctx->n_push % T);
+            int rc = some_pushes(0, n);
             if (rc != CORR_OK) return rc;
+            r = n;
         }
         const bool others = !ctx->main_set.empty() || !ctx->side_set.empty();
         int64_t q = ctx->n_push / T; // blocks that end at or before the current push
@@ -1572,14 +1642,11 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
             if (rc != CORR_OK) return rc;
         }
         while (n_steps - r >= T) {
-            // the other groups' pushes of the block, one by one
-            if (others)
-                for (int k = 0; k < T; ++k) {
-                    row(r + k);
-                    int rc = issue_push(ctx, src.data(), ctx->stream, false, true);
-                    if (rc != CORR_OK) return rc;
-                    ctx->n_push += 1;
-                }
+            // the other groups' pushes of the block
+            if (others) {
+                int rc = other_pushes(r, T);
+                if (rc != CORR_OK) return rc;
+            }
             // block q + 1 of every block-deferred group, read from the history
             for (int i : ctx->deferred_set) {
                 DeferredArgs da = deferred_args(ctx, i);
@@ -1601,8 +1668,11 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
         }
     }
     while (r < n_steps) {
-        int rc = one_push(r++);
+        const int32_t n = ctx->deferred_set.empty() ? n_steps - r
+                                                    : (int32_t)std::min<int64_t>(n_steps - r, T - ctx->n_push % T);
+        int rc = some_pushes(r, n);
         if (rc != CORR_OK) return rc;
+        r += n;
     }
     return CORR_OK;
 }

@@ -206,3 +206,40 @@ def test_multi_step_push_of_producers(corrmod):
                         c.finalize(1)
                 for i in range(4):
                     _same_readout(c.finalize(i, slice_=(0, groups[i].n_channels)), want[i], f"group {i}")
+
+
+@pytest.mark.parametrize("block", [256, 128])
+@pytest.mark.parametrize("n", [1, 1021, 100003])
+def test_replay_in_pieces(corrmod, block, n):
+    """Histories replayed in calls of every kind of length (one push, up to a
+    block boundary, across one, whole blocks, a remainder), single pushes and
+    readouts in between, with rows that are and are not 16-byte aligned: the
+    same bits as single pushes."""
+    S = 6 * block
+    say(f"[replay in pieces] n={n} block={block}")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    hist = torch.randn((S, n), generator=gen, device="cuda")
+    small = torch.randn((S, 5), generator=gen, device="cuda", dtype=torch.float64)
+    wide = torch.empty((S, n + 5), device="cuda")  # the same rows at another stride
+    wide[:, :n] = hist
+    d = corrmod.GroupDesc(n, 6, 16, 2, dtype="f32", accum="kahan")
+    e = corrmod.GroupDesc(5, 6, 16, 2, dtype="f64", accum="f64")
+    tuning = dict(tile_channels=256, chans_per_thread=2, lag_chunk=8, grid_blocks=0, fold_block=block)
+    for groups, rows in (([d], [hist]), ([d], [wide[:, :n]]), ([d, e], [hist, small]), ([e], [small])):
+        with corrmod.Correlator(groups, tuning=tuning) as c, corrmod.Correlator(groups, tuning=tuning) as ref:
+            s = 0
+            for k in (1, 63, block - 64, 1, block, 3, block + 200, block - 1, 40):
+                k = min(k, S - s)
+                if k == 3:
+                    for j in range(s, s + k):
+                        c.push([r[j] for r in rows])
+                else:
+                    c.push_steps([r[s:s + k] for r in rows])
+                for j in range(s, s + k):
+                    ref.push([r[j] for r in rows])
+                s += k
+                for i, g in enumerate(groups):
+                    kw = dict(slice_=(max(0, g.n_channels - 3), g.n_channels))
+                    if k not in (63, block - 1):  # (later folds and passes start in the middle of one)
+                        _same_readout(c.finalize(i, **kw), ref.finalize(i, **kw), f"S={s} group {i}")
+            assert c.n_pushes() == s
