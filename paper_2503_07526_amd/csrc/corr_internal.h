@@ -36,10 +36,10 @@ enum Kind : int32_t {
 
 // Pushes completed before the one being issued: the host's count, passed by
 // value, or a device counter that a captured graph's kernels read at every
-// replay.
+// replay, plus the pushes of the graph that the counter does not hold yet.
 struct StepRef {
-    const int64_t *counter; // device counter, or null: `count`
-    int64_t count;
+    const int64_t *counter; // device counter, or null
+    int64_t count;          // added to it
 };
 
 struct GroupArgs {
@@ -122,7 +122,7 @@ struct FoldStamps {
 namespace corr {
 __device__ __forceinline__ int64_t pushes_before(const StepRef &r)
 {
-    return r.counter ? *r.counter : r.count;
+    return (r.counter ? *r.counter : 0) + r.count;
 }
 __device__ __forceinline__ bool stamp_sampled(const FoldStamps *st)
 {
@@ -296,10 +296,11 @@ struct RhokMfmaArgs {
     FoldStamps *stamps;      // timing: the push's producer stamps, else null
 };
 
-// End of a push: record the scheduled flush of each block-deferred group,
-// then advance the device push counter by `advance` (1 for a push).  With
-// commit_block >= 1 the record is instead that every tile group of those
-// groups has folded block commit_block (after folds of all tile groups).
+// End of `advance` pushes (1, or up to kMultiT of a captured run): record the
+// flushes scheduled for them of each block-deferred group, then advance the
+// device push counter.  With commit_block >= 1 the record is instead that every
+// tile group of those groups has folded block commit_block (after folds of all
+// tile groups).
 struct PushEndArgs {
     int64_t *step;
     int64_t *step2;                    // a second counter advanced with step (the

@@ -387,9 +387,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void p
         lag_loop<K, CPT, LCH, false>(x, y, ring, hi, lo, slot, p, l_begin, l_end, 0, tw, lane_off);
 }
 
-// Last kernel of a push S = *step + 1: tile group S mod T of every
-// block-deferred group has folded block S / T (its flush ran earlier in this
-// push), then the counter advances.  After the folds of every tile group
+// Last kernel of a push S = *step + 1 (or of several pushes of a captured run):
+// tile group S mod T of every block-deferred group has folded block S / T (its
+// flush ran earlier in this push), then the counter advances.  After the folds of every tile group
 // (a catch-up, or a block folded from a stored history) the record is that
 // block for all tile groups, and the counter advances by the pushes the
 // launch stands for (a whole history block when no group needs per-push
@@ -437,16 +437,18 @@ __global__ void push_end_kernel(PushEndArgs a)
             for (int j = threadIdx.x; j < a.defer_t[i]; j += blockDim.x)
                 if (a.flushed[i][j] < a.commit_block) a.flushed[i][j] = a.commit_block;
     }
-    if (threadIdx.x != 0) return;
-    const int64_t S = *a.step + 1;
-    for (int i = 0; i < a.n_flushed; ++i) {
-        const int T = a.defer_t[i];
-        if (a.commit_block < 1) {
-            const int j = (int)(S % T);
-            const int64_t q = S / T;
-            if (q >= 1 && a.flushed[i][j] < q) a.flushed[i][j] = q;
+    const int64_t S = *a.step;
+    if (a.commit_block < 1)
+        for (int i = 0; i < a.n_flushed; ++i) {
+            const int T = a.defer_t[i]; // (at least the pushes of a run: distinct tile groups)
+            for (int64_t s = S + 1 + threadIdx.x; s <= S + a.advance; s += blockDim.x) {
+                const int j = (int)(s % T);
+                const int64_t q = s / T;
+                if (q >= 1 && a.flushed[i][j] < q) a.flushed[i][j] = q;
+            }
         }
-    }
+    __syncthreads(); // every thread has read the counter
+    if (threadIdx.x != 0) return;
     *a.step += a.advance;
     if (a.step2) *a.step2 += a.advance;
 }
@@ -584,7 +586,7 @@ hipError_t launch_push_window(const GroupArgs &g, StepRef step, int cpt, int lch
 
 hipError_t launch_push_end(const PushEndArgs &a, hipStream_t st)
 {
-    if (a.n_flushed < 0 || a.n_flushed > kMaxGroups || a.n_stamps < 0 || a.n_stamps > 2)
+    if (a.n_flushed < 0 || a.n_flushed > kMaxGroups || (a.commit_block < 1 && a.advance > kMultiT) || a.n_stamps < 0 || a.n_stamps > 2)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(push_end_kernel, dim3(1), dim3(64), 0, st, a);
     return hipGetLastError();

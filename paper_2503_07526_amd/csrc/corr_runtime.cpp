@@ -143,11 +143,16 @@ struct corr_ctx {
     // main_set: per-step (direct) groups fed with samples; side_set: k-density
     // groups; deferred_set (below): block-deferred groups (staged per push).
     std::vector<int> main_set, side_set; // context group indices
-    // groups updated by multi-step passes, and how many pushes wait in their
-    // rows; main_upd, side_upd: the others of main_set and side_set
-    std::vector<int> multi_set, main_upd, side_upd;
+    // groups updated by multi-step passes (in graph contexts those of a captured
+    // run of pushes only), and how many pushes wait in their rows
+    std::vector<int> multi_set;
     int32_t waiting = 0;
-    PushArgs pa_main{}, pa_side{}, pa_direct{}; // of main_upd, side_upd and both
+    // the groups that a push updates by itself: those of main_set, side_set
+    // and both (without the multi-step ones where these wait)
+    struct Upd {
+        std::vector<int> main, side;
+        PushArgs pa_main{}, pa_side{}, pa_direct{};
+    } upd, upd_run; // single pushes; pushes of a captured run
     hipStream_t side_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     hipGraph_t graph = nullptr;
@@ -414,9 +419,23 @@ int next_events(corr_ctx *c, int which, hipEvent_t *a, hipEvent_t *b)
     return CORR_OK;
 }
 
-StepRef step_main(const corr_ctx *c) { return c->counted ? StepRef{c->d_step, 0} : StepRef{nullptr, c->n_push}; }
+// A push of a captured run: its place among the (at most kMultiT) pushes that
+// end together.  each: every push has an end kernel of its own (stamps).
+struct Run {
+    int32_t row;
+    bool each;
+    int64_t before() const { return each ? 0 : row; } // pushes since the counter's
+};
+
+StepRef step_main(const corr_ctx *c, const Run *run = nullptr)
+{
+    return c->counted ? StepRef{c->d_step, run ? run->before() : 0} : StepRef{nullptr, c->n_push};
+}
 // (the sets that run on the side stream)
-StepRef step_side(const corr_ctx *c) { return c->counted ? StepRef{c->d_step_side, 0} : StepRef{nullptr, c->n_push}; }
+StepRef step_side(const corr_ctx *c, const Run *run = nullptr)
+{
+    return c->counted ? StepRef{c->d_step_side, run ? run->before() : 0} : StepRef{nullptr, c->n_push};
+}
 
 DeferredArgs deferred_args(const corr_ctx *c, int i)
 {
@@ -435,7 +454,7 @@ DeferredArgs deferred_args(const corr_ctx *c, int i)
 // (tile group S mod kDeferT folds block S / kDeferT if not done yet); with
 // events, f0/f1 bracket the fold kernels.  The flush is recorded as done by
 // the push's last kernel (push_end).
-int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1)
+int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1, const Run *run)
 {
     if (f0) HIP_TRY(c, hipEventRecord(f0, st));
     for (int i : c->deferred_set) {
@@ -449,6 +468,7 @@ int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1)
              g.flushed[(size_t)(S % g.T)] >= S / g.T))
             continue;
         DeferredArgs da = deferred_args(c, i);
+        da.step = step_main(c, run);
         da.stamps = c->d_stamps; // the catch-up flushes of a readout carry none
         HIP_TRY(c, launch_flush_fold(da, st));
     }
@@ -662,23 +682,27 @@ int add_waiting(corr_ctx *c, int64_t n_done)
 // waits for the other stream's work of the push before (the per-push fork
 // and join each left the chip idle for a few microseconds).
 int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_flush,
-               bool skip_deferred = false, bool chained = false)
+               bool skip_deferred = false, bool chained = false, const Run *run = nullptr)
 {
     // skip_deferred: the block-deferred groups take no part in this push (a
     // replay folds their block straight from the history instead)
     static const std::vector<int> none;
     const std::vector<int> &dset = skip_deferred ? none : c->deferred_set;
     if (skip_deferred) with_flush = false;
+    const corr_ctx::Upd &upd = run ? c->upd_run : c->upd;
+    const bool ends = !run || run->each; // the push has its own end kernel
     const size_t ng = c->groups.size();
     std::vector<const void *> resolved(ng);
     std::vector<void *> made(ng, nullptr); // where the producers write
     KeepArgs keep{};
     for (size_t i = 0; i < ng; ++i) {
         const Group &g = c->groups[i];
-        char *row = g.multi ? g.rows + (int64_t)c->waiting * g.row_bytes : nullptr;
+        // (the samples of a captured run stay where they are: its passes read them there)
+        const bool waits = g.multi && (run || !c->counted);
+        char *row = waits ? g.rows + (int64_t)(run ? run->row : c->waiting) * g.row_bytes : nullptr;
         if (g.produced())
             made[i] = row ? row : g.rhok_out;
-        else if (row)
+        else if (row && !run)
             keep.row[keep.n++] = KeepRow{src[i], row, (int64_t)g.input_bytes, 0};
         resolved[i] = g.produced() ? made[i] : src[i];
     }
@@ -687,9 +711,9 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     const bool timed = (c->flags & CORR_FLAG_TIMING) && st == c->stream &&
                        c->n_push % c->timing_stride == 0;
     const bool fork = c->tuning.overlap_producers == 1 && !c->side_set.empty() &&
-                      (!c->main_upd.empty() || !dset.empty());
+                      (!upd.main.empty() || !dset.empty());
     const bool fork_updates = c->tuning.overlap_producers == 2 && with_flush && !dset.empty() &&
-                              (!c->main_upd.empty() || !c->side_upd.empty());
+                              (!upd.main.empty() || !upd.side.empty());
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         int rc = next_events(c, 0, &e0, &e1);
@@ -710,7 +734,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     for (int i : dset) {
         GroupArgs ga = c->pargs.g[(size_t)i];
         ga.samples = resolved[(size_t)i];
-        HIP_TRY(c, launch_stage(ga, step_main(c), st));
+        HIP_TRY(c, launch_stage(ga, step_main(c, run), st));
     }
     hipStream_t pst = fork ? c->side_stream : st;
     for (int i : c->side_set) {
@@ -749,30 +773,30 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         // the per-step push of every direct group, sample-fed ones included,
         // in one launch after the producers: the main stream keeps only the
         // staging and the flush of the block-deferred groups
-        std::vector<int> idx(c->main_upd);
-        idx.insert(idx.end(), c->side_upd.begin(), c->side_upd.end());
-        int rc = launch_set(c, c->pa_direct, step_side(c), idx, resolved, pst);
+        std::vector<int> idx(upd.main);
+        idx.insert(idx.end(), upd.side.begin(), upd.side.end());
+        int rc = launch_set(c, upd.pa_direct, step_side(c, run), idx, resolved, pst);
         if (rc != CORR_OK) return rc;
-        if (chained) {
+        if (chained && ends) {
             PushEndArgs se{};
             se.step = c->d_step_side;
             se.advance = 1;
             se.stamps = c->d_stamps ? c->d_stamps + 1 : nullptr;
             se.n_stamps = 1;
             HIP_TRY(c, launch_push_end(se, pst));
-        } else {
+        } else if (!chained) {
             HIP_TRY(c, hipEventRecord(c->ev_join, pst));
         }
     } else if (fork) {
         // no flush to overlap: the sample-fed groups run beside the producers
-        int rc = launch_set(c, c->pa_side, step_side(c), c->side_upd, resolved, pst);
+        int rc = launch_set(c, upd.pa_side, step_side(c, run), upd.side, resolved, pst);
         if (rc != CORR_OK) return rc;
         HIP_TRY(c, hipEventRecord(c->ev_join, pst));
-        rc = launch_set(c, c->pa_main, step_main(c), c->main_upd, resolved, st);
+        rc = launch_set(c, upd.pa_main, step_main(c, run), upd.main, resolved, st);
         if (rc != CORR_OK) return rc;
     } else {
-        std::vector<int> idx(c->main_upd);
-        idx.insert(idx.end(), c->side_upd.begin(), c->side_upd.end());
+        std::vector<int> idx(upd.main);
+        idx.insert(idx.end(), upd.side.begin(), upd.side.end());
         if (!idx.empty()) {
             hipStream_t ust = st;
             if (fork_updates) {
@@ -780,7 +804,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
                 HIP_TRY(c, hipStreamWaitEvent(c->side_stream, c->ev_fork, 0));
                 ust = c->side_stream;
             }
-            int rc = launch_set(c, c->pa_direct, step_side(c), idx, resolved, ust);
+            int rc = launch_set(c, upd.pa_direct, step_side(c, run), idx, resolved, ust);
             if (rc != CORR_OK) return rc;
             if (fork_updates) HIP_TRY(c, hipEventRecord(c->ev_join, ust));
         }
@@ -791,17 +815,17 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
             int rc = next_events(c, 1, &f0, &f1);
             if (rc != CORR_OK) return rc;
         }
-        int rc = launch_flushes(c, st, f0, f1);
+        int rc = launch_flushes(c, st, f0, f1, run);
         if (rc != CORR_OK) return rc;
     }
     if (fork_updates) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     if (fork && !chained) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
-    if (!c->multi_set.empty() && ++c->waiting == kMultiT) {
+    if (!c->counted && !c->multi_set.empty() && ++c->waiting == kMultiT) {
         int rc = add_waiting(c, c->n_push + 1);
         if (rc != CORR_OK) return rc;
     }
-    if (!c->counted) return CORR_OK;
+    if (!c->counted || !ends) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
     pe.step2 = chained ? nullptr : c->d_step_side;
@@ -845,6 +869,37 @@ int capture_graph(corr_ctx *c)
     c->gexec = nullptr;
     c->graph = nullptr;
     return capture_one(c, !c->deferred_set.empty(), &c->graph, &c->gexec);
+}
+
+// End n captured pushes, the rows [r0, r0 + n) of the histories: the
+// multi-step passes on `ust`, then, unless every push had its own, the end
+// kernels (chained: of the main and of the side stream).
+int end_run(corr_ctx *c, const void *const *samples, const std::vector<int64_t> &stride, int32_t r0, int32_t n,
+            bool each, bool chained, hipStream_t ust)
+{
+    for (int i : c->multi_set) {
+        const Group &g = c->groups[(size_t)i];
+        const char *hist = static_cast<const char *>(samples[i]) + (int64_t)r0 * stride[(size_t)i];
+        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{c->d_step_side, each ? -(int64_t)n : 0},
+                                     g.produced() ? g.rows : hist, g.produced() ? g.row_bytes : stride[(size_t)i],
+                                     n, ust));
+    }
+    if (each) return CORR_OK;
+    PushEndArgs pe{};
+    pe.step = c->d_step;
+    pe.advance = n;
+    for (int i : c->deferred_set) {
+        pe.defer_t[pe.n_flushed] = c->groups[(size_t)i].T;
+        pe.flushed[pe.n_flushed++] = c->groups[(size_t)i].d_flushed;
+    }
+    if (!chained) pe.step2 = c->d_step_side;
+    HIP_TRY(c, launch_push_end(pe, c->cap_stream));
+    if (!chained) return CORR_OK;
+    PushEndArgs se{};
+    se.step = c->d_step_side;
+    se.advance = n;
+    HIP_TRY(c, launch_push_end(se, c->side_stream));
+    return CORR_OK;
 }
 
 int ensure_scratch(corr_ctx *c, size_t bytes)
@@ -1296,11 +1351,11 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
         if (g.deferred) c->deferred_set.push_back(i);
         tile_first += g.n_tiles;
     }
-    // Per-step groups whose pushes wait for multi-step passes: not where a
-    // captured graph or the timing takes every push by itself, nor in the
-    // contrast forms; the waiting rows take at most a sixteenth of the free
-    // memory.  The sums are the same bit for bit either way.
-    if (!c->counted && !(flags & (CORR_FLAG_DIRECT | CORR_FLAG_PER_GROUP))) {
+    // Per-step groups whose pushes wait for multi-step passes: not where the
+    // timing takes every push by itself (the pushes of a captured run do wait),
+    // nor in the contrast forms; the waiting rows take at most a sixteenth of
+    // the free memory.  The sums are the same bit for bit either way.
+    if ((!c->counted || (flags & CORR_FLAG_GRAPH)) && !(flags & (CORR_FLAG_DIRECT | CORR_FLAG_PER_GROUP))) {
         size_t free_b = 0, total_b = 0, left = 0;
         if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) left = free_b / 16;
         for (int i = 0; i < n_groups; ++i) {
@@ -1329,14 +1384,17 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
             c->side_set.push_back(i);
         else if (!g.deferred)
             c->main_set.push_back(i);
-        if (g.multi || g.deferred) continue;
-        (g.produced() ? c->side_upd : c->main_upd).push_back(i);
     }
-    {
-        std::vector<int> both(c->main_upd);
-        both.insert(both.end(), c->side_upd.begin(), c->side_upd.end());
-        const std::vector<int> *sets[3] = {&c->main_upd, &c->side_upd, &both};
-        PushArgs *pas[3] = {&c->pa_main, &c->pa_side, &c->pa_direct};
+    for (corr_ctx::Upd *u : {&c->upd, &c->upd_run}) {
+        for (int i = 0; i < n_groups; ++i) {
+            const Group &g = c->groups[(size_t)i];
+            if (g.deferred || (g.multi && (u == &c->upd_run || !c->counted))) continue;
+            (g.produced() ? u->side : u->main).push_back(i);
+        }
+        std::vector<int> both(u->main);
+        both.insert(both.end(), u->side.begin(), u->side.end());
+        const std::vector<int> *sets[3] = {&u->main, &u->side, &both};
+        PushArgs *pas[3] = {&u->pa_main, &u->pa_side, &u->pa_direct};
         for (int pass = 0; pass < 3; ++pass) {
             const std::vector<int> &idx = *sets[pass];
             PushArgs &pa = *pas[pass];
@@ -1514,9 +1572,16 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
                 cap(hipEventRecord(ctx->ev_fork, ctx->cap_stream), "hipEventRecord");
                 cap(hipStreamWaitEvent(ctx->side_stream, ctx->ev_fork, 0), "hipStreamWaitEvent");
             }
+            // Pushes end together, up to kMultiT of them: the multi-step
+            // passes of the groups whose samples waited, then the end kernels
+            // (one per chain; after every push where it carries stamps).
+            hipStream_t ust = chained ? ctx->side_stream : ctx->cap_stream;
             for (int32_t r = 0; r < n_steps && rc == CORR_OK; ++r) {
                 row(r);
-                rc = issue_push(ctx, src.data(), ctx->cap_stream, with_flush, false, chained);
+                const Run run{r % kMultiT, ctx->d_stamps != nullptr};
+                rc = issue_push(ctx, src.data(), ctx->cap_stream, with_flush, false, chained, &run);
+                if (rc == CORR_OK && (run.row + 1 == kMultiT || r + 1 == n_steps))
+                    rc = end_run(ctx, samples, stride, r - run.row, run.row + 1, run.each, chained, ust);
                 if (chained && rc == CORR_OK && (r + 1) % kChainSync == 0 && r + 1 < n_steps) {
                     cap(hipEventRecord(ctx->ev_join, ctx->side_stream), "hipEventRecord");
                     cap(hipStreamWaitEvent(ctx->cap_stream, ctx->ev_join, 0), "hipStreamWaitEvent");
@@ -1562,7 +1627,7 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
     // The pushes of rows [r0, r0 + n) for the groups that are not
     // block-deferred.  Sample groups with multi-step passes take them from the
     // history when no other group needs a launch for every push.
-    const bool each_push = ctx->counted || !ctx->side_set.empty() || !ctx->main_upd.empty();
+    const bool each_push = ctx->counted || !ctx->side_set.empty() || !ctx->upd.main.empty();
     auto other_pushes = [&](int32_t r0, int32_t n) -> int {
         if (!each_push) {
             int rc = add_waiting(ctx, ctx->n_push);

@@ -243,3 +243,43 @@ def test_replay_in_pieces(corrmod, block, n):
                     if k not in (63, block - 1):  # (later folds and passes start in the middle of one)
                         _same_readout(c.finalize(i, **kw), ref.finalize(i, **kw), f"S={s} group {i}")
             assert c.n_pushes() == s
+
+
+@pytest.mark.parametrize("overlap", [0, 1, 2])
+@pytest.mark.parametrize("timing", [False, True])
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_captured_runs(corrmod, overlap, timing, k):
+    """Captured runs of pushes (shorter and longer than a multi-step pass and
+    than a fold block), each replayed several times with single pushes, other
+    runs and readouts in between: the same bits as single pushes of the
+    per-group form."""
+    N, nk, box, R, n = 500, 30, 30.0, 150, 700
+    say(f"[captured runs] overlap={overlap} timing={timing} groups={k}")
+    kv = synth.kvectors(nk)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    pos = box * torch.rand((R, 3 * N), generator=gen, device="cuda")
+    vel = torch.randn((R, 3 * N), generator=gen, device="cuda")
+    q = torch.randn((R, 3), generator=gen, device="cuda")
+    groups = [corrmod.GroupDesc(nk, 6, 32, 2, dtype="cf32", accum="kahan", source="rhok", kvec=kv, n_atoms=N, box=box),
+              corrmod.GroupDesc(9, 8, 16, 2, dtype="f64", accum="f64"),
+              corrmod.GroupDesc(n, 6, 16, 2, dtype="f32", accum="kahan"),
+              corrmod.GroupDesc(6, 6, 16, 2, dtype="f32", accum="kahan", source="momentum", n_atoms=N, box=box,
+                                species=np.arange(N, dtype=np.int32) % 2, masses=np.array([2.0, 3.0]), pair=True),
+              corrmod.GroupDesc(40, 1, 600, 2, dtype="f32", accum="kahan")][:k]
+    rows = [pos, torch.randn((R, 9), generator=gen, device="cuda", dtype=torch.float64),
+            torch.randn((R, n), generator=gen, device="cuda"), torch.cat([vel, q, q], 1),
+            torch.randn((R, 40), generator=gen, device="cuda")][:k]
+    tuning = dict(tile_channels=256, chans_per_thread=2, lag_chunk=8, grid_blocks=0, overlap_producers=overlap,
+                  fold_block=128)
+    with corrmod.Correlator(groups, graph=True, timing=timing, tuning=tuning) as c, \
+            corrmod.Correlator(groups, per_group=True, tuning=tuning) as ref:
+        for b, e in ((0, 16), (0, 16), (0, 16), (3, 4), (10, 75), (10, 75), (0, 150), (0, 16), (0, 150), (5, 69)):
+            c.push_steps([r[b:e] for r in rows])
+            if e == 75:  # a push by itself between the runs
+                c.push([r[7] for r in rows])
+            for j in list(range(b, e)) + ([7] if e == 75 else []):
+                ref.push([r[j] for r in rows])
+            if b in (3, 10, 5) or e == 150:
+                for i, g in enumerate(groups):
+                    kw = dict(slice_=(0, min(g.n_channels, 40)))
+                    _same_readout(c.finalize(i, **kw), ref.finalize(i, **kw), f"[{b}, {e}) group {i}")
