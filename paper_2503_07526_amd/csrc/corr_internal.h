@@ -276,7 +276,7 @@ struct RhokMfmaArgs {
     const int32_t *slot_k;   // nw == 3: [pair][16 |n_z|][n_z < 0]; nw == 1:
                              // [couple][16 |n_z|][n_y < 0][n_z < 0]: k index
                              // stored for the slot, or -1
-    const int32_t *k_src;    // [nk]: partial row that holds k's sum
+    const int32_t *k_src;    // [nk]: partial row that holds k's sum; null: row k
     int32_t n_mtiles;
     int32_t nmax;            // max |n component|, at most 15
     int32_t x_lo, x_rows;    // table rows: n_x in [x_lo, x_lo + x_rows) over the rows

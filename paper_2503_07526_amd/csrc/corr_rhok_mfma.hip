@@ -49,6 +49,7 @@
 #include <hip/hip_runtime.h>
 
 #include "corr_kernels.h"
+#include "corr_wave.h"
 
 namespace corr {
 
@@ -1043,52 +1044,76 @@ void rhok_couple_kernel(RhokMfmaArgs a)
 // twice reads the partials stored under its first index).  NW = 1: n(k).
 // NW = 3: the current vector J(k), stored as its components on the k-vector's
 // basis (khat, e1, e2) at channels 3k, 3k+1, 3k+2.
+// A chain of latencies (2048 k-vectors: 8 MB in 5 us): the partials are loaded
+// four blocks ahead of their additions, and the 2 NW sums over the lanes share
+// their exchanges (currents of 2048 k-vectors 6.2 -> 4.8 us, of 512 7.3 -> 4.7;
+// n(k) of 300 3.3 -> 2.5).
 template <int NW>
 __global__ __launch_bounds__(256) void rhok_mfma_final_kernel(RhokMfmaArgs a)
 {
     const int k = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (k >= a.nk) return; // whole wave
-    const size_t row = (size_t)a.k_src[k];
+    const size_t row = a.k_src ? (size_t)a.k_src[k] : (size_t)k;
+    double bas[3] = {0.0, 0.0, 0.0}; // lanes 0 .. 2: their row of the basis
+    if constexpr (NW == 3) {
+        if (lane < 3) {
+#pragma unroll
+            for (int w = 0; w < 3; ++w) bas[w] = a.basis[(size_t)k * 9 + 3 * lane + w];
+        }
+    }
     double sr[NW], si[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const double *src = a.partial + (row * NW + w) * a.n_atom_blocks * 2;
-        double r = 0.0, i = 0.0;
-        for (int b = lane; b < a.n_atom_blocks; b += 64) {
-            r += src[2 * b];
-            i += src[2 * b + 1];
-        }
+    for (int w = 0; w < NW; ++w) sr[w] = si[w] = 0.0;
+    const double2 *src = reinterpret_cast<const double2 *>(a.partial) + row * NW * a.n_atom_blocks;
+    constexpr int U = 4;
+    for (int b0 = lane; b0 < a.n_atom_blocks; b0 += 64 * U) {
+        double2 v[NW][U];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            r += __shfl_down(r, off, 64);
-            i += __shfl_down(i, off, 64);
-        }
-        sr[w] = r;
-        si[w] = i;
-    }
-    if (lane != 0) return;
-    if (a.stamps) stamp_end(a.stamps, (unsigned)k);
-    if constexpr (NW == 1) {
-        if (a.out_double)
-            static_cast<double2 *>(a.out)[k] = make_double2(sr[0], si[0]);
-        else
-            static_cast<float2 *>(a.out)[k] = make_float2((float)sr[0], (float)si[0]);
-    } else {
-        const double *bas = a.basis + (size_t)k * 9;
+        for (int w = 0; w < NW; ++w)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double r = 0.0, i = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                r += bas[3 * c + w] * sr[w];
-                i += bas[3 * c + w] * si[w];
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + 64 * u;
+                v[w][u] = b < a.n_atom_blocks ? src[(size_t)w * a.n_atom_blocks + b] : make_double2(0.0, 0.0);
             }
-            if (a.out_double)
-                static_cast<double2 *>(a.out)[3 * k + c] = make_double2(r, i);
-            else
-                static_cast<float2 *>(a.out)[3 * k + c] = make_float2((float)r, (float)i);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int u = 0; u < U; ++u) { // (the sums are never -0: a missing block adds nothing)
+                sr[w] += v[w][u].x;
+                si[w] += v[w][u].y;
+            }
+    }
+    if constexpr (NW == 1) {
+        // lanes 0 .. 31 the real part, 32 .. 63 the imaginary part
+        double s = pair_fold<32>(sr[0], si[0]);
+        s = pair_fold<16>(s, s);
+        s += lane_xor<8>(s);
+        s += lane_xor<4>(s);
+        s += lane_xor<2>(s);
+        s += lane_xor<1>(s);
+        if (a.stamps && lane == 0) stamp_end(a.stamps, (unsigned)k);
+        if ((lane & 31) != 0) return;
+        const size_t i = 2 * (size_t)k + (lane >> 5);
+        if (a.out_double)
+            static_cast<double *>(a.out)[i] = s;
+        else
+            static_cast<float *>(a.out)[i] = (float)s;
+    } else {
+        const double v[8] = {sr[0], si[0], sr[1], si[1], sr[2], si[2], 0.0, 0.0};
+        const double s = wave_sums<8>(v); // lane l: value l / 8
+        double r = 0.0, i = 0.0;          // lanes 0 .. 2: component `lane`
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+            r += bas[w] * __shfl(s, 16 * w, 64);
+            i += bas[w] * __shfl(s, 16 * w + 8, 64);
         }
+        if (a.stamps && lane == 0) stamp_end(a.stamps, (unsigned)k);
+        if (lane >= 3) return;
+        if (a.out_double)
+            static_cast<double2 *>(a.out)[3 * k + lane] = make_double2(r, i);
+        else
+            static_cast<float2 *>(a.out)[3 * k + lane] = make_float2((float)r, (float)i);
     }
 }
 

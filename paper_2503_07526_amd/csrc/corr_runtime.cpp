@@ -1220,7 +1220,9 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
                 r.pair_nx = g.d_mtab;
                 r.pair_ny = r.pair_nx + pnx.size();
                 r.slot_k = r.pair_ny + pny.size();
-                r.k_src = r.slot_k + slot_k.size();
+                bool own_rows = true; // no k-vector listed twice
+                for (int q = 0; q < nk; ++q) own_rows = own_rows && k_src[(size_t)q] == q;
+                r.k_src = own_rows ? nullptr : r.slot_k + slot_k.size();
                 r.n_mtiles = n_mtiles;
                 r.nmax = nmax;
                 r.x_lo = x_lo;
