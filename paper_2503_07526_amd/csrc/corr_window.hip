@@ -188,7 +188,7 @@ __global__ __launch_bounds__(512) void window_fold_kernel(GroupArgs g0, GroupArg
     const int64_t tile_bytes = second ? g1.tile_bytes : g0.tile_bytes;
     char *const state = second ? g1.state : g0.state;
     const S *const samples = static_cast<const S *>(second ? g1.samples : g0.samples);
-    const int wave = (int)(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     const int64_t ch = (int64_t)((int)blockIdx.x - (second ? x1 : 0)) * 64 + lane;
     const int64_t tile = ch / tw;
@@ -215,9 +215,27 @@ __global__ __launch_bounds__(512) void window_fold_kernel(GroupArgs g0, GroupArg
     const int span = nwaves * LB;
     const int64_t v_lo = s0 - Lb0 - (span - 1);
     const int n_rows = 2 * T + span - 1;
-    for (int r = wave; r < n_rows; r += nwaves) {
-        const int64_t v = r < T ? s0 + r : v_lo + (r - T);
-        rows[(size_t)r * 64 + lane] = v == P ? xP : ring[(size_t)wrap_slot(v, p0) * tw];
+    // One modulo each for the new and the lagged rows, then a wrap per row
+    // (fewer rows than slots), the rows taken eight at a time.  With a 64-bit
+    // modulo per row and lane and one row at a time the fold of 2048 channels
+    // at p = 4096 took 16 us instead of 10, of 8192 at p = 10240 42 instead of 13.
+    const int sN = wrap_slot(s0, p0), sL = wrap_slot(v_lo, p0);
+    constexpr int B = 8;
+    for (int r0 = wave; r0 < n_rows; r0 += B * nwaves) {
+        S x[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int r = min(r0 + u * nwaves, n_rows - 1);
+            int slot = r < T ? sN + r : sL + (r - T);
+            if (slot >= p0) slot -= p0;
+            x[u] = ring[(size_t)slot * tw];
+            if ((r < T ? s0 + r : v_lo + (r - T)) == P) x[u] = xP;
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int r = r0 + u * nwaves;
+            if (r < n_rows) rows[(size_t)r * 64 + lane] = x[u];
+        }
     }
     __syncthreads();
     if (L0 >= lag_end) return; // this wave's lags are past the lag block
