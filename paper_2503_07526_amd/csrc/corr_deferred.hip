@@ -231,7 +231,7 @@ __device__ __forceinline__ void levels01(Ctx &cx, typename RK<K>::S *out)
     const int n1 = has1 ? r / 2 : 0;    // level-1 values of this pass
     const int64_t f1 = f >> 1;          // level-1 values already in the ring
     // level 0: value j in slot (j - 1) mod P0 (one modulo, then a wrap per row)
-    const int slot0 = (int)((f - (P - 2) - 1 + P0) % P0);
+    const int slot0 = slot_of(f - (P - 2) - 1 + P0, P0);
     auto row0 = [&](int i) -> S {
         int slot = slot0 + i;
         if (slot >= P0) slot -= P0;
@@ -330,7 +330,7 @@ __device__ __forceinline__ void levels01(Ctx &cx, typename RK<K>::S *out)
         // the block's last P - 1 values (now W0[0 .. P-2]) go to their ring
         // slots: the next block's folds and the readouts look back to them
         S *ring0w = reinterpret_cast<S *>(cx.tb);
-        const int slot_w = (int)((f + T - (P - 1)) % P0); // value f + T - P + 2
+        const int slot_w = slot_of(f + T - (P - 1), P0); // value f + T - P + 2
 #pragma unroll
         for (int i = 0; i < P - 1; ++i) {
             int slot = slot_w + i;
@@ -649,6 +649,7 @@ hipError_t launch_deferred_t(const DeferredArgs &a, hipStream_t st)
 // loads issued before the stores.
 constexpr int kStageVec = 4;
 constexpr int kStageUnroll = 4;
+constexpr int64_t kStageMaxChannels = (int64_t)1 << 28; // (tile_div; their state would exceed 500 GB)
 
 // The sample is read once, and its ring row is read again only by the fold
 // of its subset: in the same push for one subset in T, up to T pushes (and
@@ -657,45 +658,52 @@ constexpr int kStageUnroll = 4;
 // (the large step 0.244 against 0.253 ms).
 typedef float stage_f4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, int aligned)
+// Vectors of a tile of the stage kernels: vector v lies in tile v / d at
+// vector v % d, d = tw / kStageVec (16 .. 1024), by a multiplication (exact for
+// v (d - 1) < 2^36, v < 2^31: launch_stage checks n_ch < 2^28).  With a 64-bit
+// division a vector (most of the kernel's instructions) a push of 250047, 3e6
+// and 1.2e7 channels took 3.2, 7.2 and 20.6 us instead of 3.0, 6.7 and 19.8
+// (4.8 TB/s).
+struct TileDiv {
+    uint64_t mul; // ceil(2^36 / d)
+    uint32_t d;
+    uint32_t pad_;
+};
+
+__device__ __forceinline__ float *stage_row(const GroupArgs &g, const TileDiv &td, uint32_t v, int slot)
 {
-    const int64_t s = pushes_before(step) + 1;
-    const int slot = (int)((s - 1) % g.p0);
+    const uint32_t tile = (uint32_t)((v * td.mul) >> 36);
+    const uint32_t lane = (v - tile * td.d) * kStageVec;
+    return reinterpret_cast<float *>(g.state + tile * g.tile_bytes) + (size_t)slot * g.tw + lane;
+}
+
+// Four channels of the input from vector v on; channels past the end read as 0.
+__device__ __forceinline__ stage_f4 stage_load(const float *src, int64_t n, uint32_t v, int aligned)
+{
+    const int64_t c = (int64_t)v * kStageVec;
+    if (aligned && c + kStageVec <= n)
+        return __builtin_nontemporal_load(reinterpret_cast<const stage_f4 *>(src + c));
+    stage_f4 x;
+#pragma unroll
+    for (int i = 0; i < kStageVec; ++i) x[i] = c + i < n ? src[c + i] : 0.f;
+    return x;
+}
+
+__global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, TileDiv td, int aligned)
+{
+    const int slot = slot_of(pushes_before(step), g.p0);
     const float *src = static_cast<const float *>(g.samples);
-    const int64_t n = g.n_ch;
-    const int64_t nvec = (n + kStageVec - 1) / kStageVec;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v0 < nvec;
-         v0 += stride * kStageUnroll) {
-        float4 x[kStageUnroll];
+    const uint32_t nvec = (uint32_t)((g.n_ch + kStageVec - 1) / kStageVec);
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t v0 = blockIdx.x * blockDim.x + threadIdx.x; v0 < nvec; v0 += stride * kStageUnroll) {
+        stage_f4 x[kStageUnroll];
 #pragma unroll
-        for (int u = 0; u < kStageUnroll; ++u) {
-            const int64_t v = v0 + u * stride;
-            const int64_t c = v * kStageVec;
-            if (v < nvec) {
-                if (aligned && c + kStageVec <= n) {
-                    const stage_f4 t = __builtin_nontemporal_load(reinterpret_cast<const stage_f4 *>(src + c));
-                    x[u] = make_float4(t[0], t[1], t[2], t[3]);
-                } else {
-                    x[u].x = c + 0 < n ? src[c + 0] : 0.f;
-                    x[u].y = c + 1 < n ? src[c + 1] : 0.f;
-                    x[u].z = c + 2 < n ? src[c + 2] : 0.f;
-                    x[u].w = c + 3 < n ? src[c + 3] : 0.f;
-                }
-            }
-        }
+        for (int u = 0; u < kStageUnroll; ++u)
+            if (v0 + u * stride < nvec) x[u] = stage_load(src, g.n_ch, v0 + u * stride, aligned);
 #pragma unroll
-        for (int u = 0; u < kStageUnroll; ++u) {
-            const int64_t v = v0 + u * stride;
-            if (v < nvec) {
-                const int64_t c = v * kStageVec;
-                const int64_t tile = c / g.tw;
-                const int64_t lane = c - tile * g.tw;
-                float *ring = reinterpret_cast<float *>(g.state + tile * g.tile_bytes);
-                __builtin_nontemporal_store(stage_f4{x[u].x, x[u].y, x[u].z, x[u].w},
-                                            reinterpret_cast<stage_f4 *>(ring + (size_t)slot * g.tw + lane));
-            }
-        }
+        for (int u = 0; u < kStageUnroll; ++u)
+            if (v0 + u * stride < nvec)
+                __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(stage_row(g, td, v0 + u * stride, slot)));
     }
 }
 
@@ -704,37 +712,35 @@ __global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, i
 // rows are neighbours in the tile; blockIdx.y counts the row quads.
 // 244 pushes of 900000 channels take 321 us (5.5 TB/s) instead of 4.4 us each
 // (1.6 TB/s) as launches of their own.
-__global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef step, int64_t pitch,
+__global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef step, TileDiv td, int64_t pitch,
                                                           int n_rows, int aligned)
 {
     const int r0 = (int)blockIdx.y * kStageUnroll;
-    const int slot0 = (int)((pushes_before(step) + r0) % g.p0);
-    const int64_t n = g.n_ch;
-    const int64_t nvec = (n + kStageVec - 1) / kStageVec;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
-        const int64_t c = v * kStageVec;
-        const int64_t tile = c / g.tw;
-        const int64_t lane = c - tile * g.tw;
-        float *ring = reinterpret_cast<float *>(g.state + tile * g.tile_bytes) + lane;
+    const int slot0 = slot_of(pushes_before(step) + r0, g.p0);
+    const uint32_t nvec = (uint32_t)((g.n_ch + kStageVec - 1) / kStageVec);
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
         stage_f4 x[kStageUnroll];
 #pragma unroll
-        for (int u = 0; u < kStageUnroll; ++u) {
-            if (r0 + u >= n_rows) continue;
-            const float *src = reinterpret_cast<const float *>(static_cast<const char *>(g.samples) + (r0 + u) * pitch);
-            if (aligned && c + kStageVec <= n)
-                x[u] = __builtin_nontemporal_load(reinterpret_cast<const stage_f4 *>(src + c));
-            else
-                for (int i = 0; i < kStageVec; ++i) x[u][i] = c + i < n ? src[c + i] : 0.f;
-        }
+        for (int u = 0; u < kStageUnroll; ++u)
+            if (r0 + u < n_rows)
+                x[u] = stage_load(reinterpret_cast<const float *>(static_cast<const char *>(g.samples) + (r0 + u) * pitch),
+                                  g.n_ch, v, aligned);
+        float *row = stage_row(g, td, v, 0);
 #pragma unroll
         for (int u = 0; u < kStageUnroll; ++u) {
             if (r0 + u >= n_rows) continue;
             int slot = slot0 + u;
             if (slot >= g.p0) slot -= g.p0;
-            __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(ring + (size_t)slot * g.tw));
+            __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(row + (size_t)slot * g.tw));
         }
     }
+}
+
+TileDiv tile_div(const GroupArgs &g)
+{
+    const uint32_t d = (uint32_t)g.tw / kStageVec;
+    return TileDiv{(((uint64_t)1 << 36) + d - 1) / d, d, 0};
 }
 
 } // namespace
@@ -743,24 +749,25 @@ hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st)
 {
     // single-precision samples only (the deferred form's kinds); 16-byte
     // vectors need a 16-byte aligned source
+    if (g.n_ch >= kStageMaxChannels) return hipErrorInvalidValue;
     const int aligned = ((uintptr_t)g.samples % 16) == 0;
     const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
     int64_t blocks = (nvec + 255) / 256;
     if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g, step, aligned);
+    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g, step, tile_div(g), aligned);
     return hipGetLastError();
 }
 
 hipError_t launch_stage_rows(const GroupArgs &g, StepRef step, int64_t pitch, int n_rows, hipStream_t st)
 {
-    if (n_rows < 1 || n_rows > g.p0) return hipErrorInvalidValue;
+    if (n_rows < 1 || n_rows > g.p0 || g.n_ch >= kStageMaxChannels) return hipErrorInvalidValue;
     const int aligned = ((uintptr_t)g.samples % 16) == 0 && pitch % 16 == 0;
     const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
     int64_t blocks = (nvec + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     const unsigned quads = (unsigned)((n_rows + kStageUnroll - 1) / kStageUnroll);
-    hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)blocks, quads), dim3(256), 0, st, g, step, pitch,
-                       n_rows, aligned);
+    hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)blocks, quads), dim3(256), 0, st, g, step, tile_div(g),
+                       pitch, n_rows, aligned);
     return hipGetLastError();
 }
 

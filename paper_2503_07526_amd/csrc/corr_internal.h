@@ -124,6 +124,12 @@ __device__ __forceinline__ int64_t pushes_before(const StepRef &r)
 {
     return (r.counter ? *r.counter : 0) + r.count;
 }
+// v mod n (v >= 0, n > 0), uniform over the wave: 32-bit where v allows it (a
+// 64-bit modulo is a long chain of scalar instructions).
+__device__ __forceinline__ int slot_of(int64_t v, int n)
+{
+    return ((uint64_t)v >> 32) == 0 ? (int)((uint32_t)v % (uint32_t)n) : (int)(v % n);
+}
 __device__ __forceinline__ bool stamp_sampled(const FoldStamps *st)
 {
     return *st->step % st->stride == 0;

@@ -153,10 +153,8 @@ constexpr int kWinU = 8;
 
 __device__ __forceinline__ int wrap_slot(int64_t v, int p0)
 {
-    // slot of value v (1-based; v may be <= 0): (v - 1) mod p0 in [0, p0)
-    int64_t r = (v - 1) % p0;
-    if (r < 0) r += p0;
-    return (int)r;
+    // slot of value v (1-based; v may be <= 0, but not below 1 - p0): (v - 1) mod p0
+    return slot_of(v - 1 + p0, p0);
 }
 
 // Blocks x < x1 fold window g0, the others window g1 (two windows of one
