@@ -263,7 +263,7 @@ struct MomentumArgs {
     int32_t n_species;       // 1 .. kMomMaxSpecies
     int32_t dbl;             // 1: double velocities and output
     double scale[kMomMaxSpecies];
-    double *partial;         // [n_blocks][3 kMomMaxSpecies] block sums
+    double *partial;         // [3 n_species][n_blocks] block sums
     int32_t n_blocks;
     int32_t pair;            // 1: output [2][n_ch], x copied from the input
     int32_t vec4;            // 1: n_atoms % 4 == 0 and vel 16-byte aligned (4 atoms per load)

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include "corr_kernels.h"
+#include "corr_wave.h"
 
 namespace corr {
 
@@ -91,38 +92,51 @@ template <typename T> __global__ __launch_bounds__(kMomThreads) void momentum_pa
         for (int64_t i = first; i < n; i += stride)
             add_atom(acc, ns, a.species[i], (double)v[i], (double)v[n + i], (double)v[2 * n + i]);
     }
-    // wave sums (lane 0 ends with the wave's sum), then waves in order
+    // wave sums, eight at a time (lane 8 q ends with sum q of the eight), then
+    // waves in order
     __shared__ double wsum[kMomThreads / 64][kMomSums];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q < kMomSums; ++q) {
-        if (q < 3 * ns) {
-            double x = acc[q];
+    for (int q0 = 0; q0 < kMomSums; q0 += 8) {
+        if (q0 < 3 * ns) {
+            double v8[8];
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) x += __shfl_down(x, off, 64);
-            if (lane == 0) wsum[wave][q] = x;
+            for (int q = 0; q < 8; ++q) v8[q] = acc[q0 + q];
+            const double x = wave_sums<8>(v8);
+            if ((lane & 7) == 0) wsum[wave][q0 + lane / 8] = x;
         }
     }
     __syncthreads();
     if ((int)threadIdx.x < 3 * ns) {
         double x = 0.0;
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) x += wsum[w][threadIdx.x];
-        a.partial[(size_t)blockIdx.x * kMomSums + threadIdx.x] = x;
+        a.partial[(size_t)threadIdx.x * a.n_blocks + blockIdx.x] = x;
     }
 }
 
 // One wave per channel (block q): lane l adds the block sums l, l + 64, ...
-// in order, then the wave adds its lanes by shuffles in a fixed order.
+// in order (at most kMomMaxBlocks / 64, all loaded first), then the wave adds
+// its lanes in a fixed order.
 template <typename T> __global__ __launch_bounds__(64) void momentum_final_kernel(MomentumArgs a)
 {
     const int q = blockIdx.x;
     const int nch = 3 * a.n_species;
     const int lane = threadIdx.x;
-    double x = 0.0;
-#pragma unroll 4
-    for (int b = lane; b < a.n_blocks; b += 64) x += a.partial[(size_t)b * kMomSums + q];
+    constexpr int N = kMomMaxBlocks / 64;
+    double v[N], x = 0.0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_down(x, off, 64);
+    for (int u = 0; u < N; ++u) {
+        const int b = lane + 64 * u;
+        v[u] = b < a.n_blocks ? a.partial[(size_t)q * a.n_blocks + b] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) x += v[u]; // (never -0: a missing block adds nothing)
+    x = pair_fold<32>(x, x);
+    x = pair_fold<16>(x, x);
+    x += lane_xor<8>(x);
+    x += lane_xor<4>(x);
+    x += lane_xor<2>(x);
+    x += lane_xor<1>(x);
     if (lane != 0) return;
     if (a.stamps) stamp_end(a.stamps, (unsigned)q);
     T *out = static_cast<T *>(a.out);
