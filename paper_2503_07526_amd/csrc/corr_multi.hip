@@ -18,7 +18,7 @@
 // loaded while a level is summed.
 //
 // Memory-bound for large groups (64 pushes move about 5 KB per pair channel of
-// p = 32 and 10 levels instead of 64 KB: 99999 channels 150 us a pass, against
+// p = 32 and 10 levels instead of 64 KB: 99999 channels 126 us a pass, against
 // 64 pushes of 15 us), a chain of about log2(64) short levels for small ones
 // (300 complex channels, p = 32: 31 us against 64 x 6; nine double ones, p = 16
 // and 20 levels: 13 us against 64 x 4).
@@ -142,8 +142,13 @@ __device__ __forceinline__ void add_level(LevelRegs<K, P> &r, const Level<K, P, 
         }
 }
 
+// Waves per SIMD the registers are held to: five blocks a CU for single real
+// sums (99999 pairs at p = 32: 126 us against 146 with four, and 144 with six,
+// which spill); the wider types, whose registers would not fit, are left alone.
+template <int K> constexpr int kMultiWaves = sizeof(typename KT<K>::A) == 4 ? 5 : 1;
+
 template <int K, int P, bool PAIR>
-__global__ __launch_bounds__(kMultiThreads) void multi_push_kernel(GroupArgs g, StepRef step,
+__global__ __launch_bounds__(kMultiThreads) __attribute__((amdgpu_waves_per_eu(kMultiWaves<K>))) void multi_push_kernel(GroupArgs g, StepRef step,
                                                                     const char *rows, int64_t stride, int n_rows)
 {
     using S = typename KT<K>::S;
