@@ -649,7 +649,7 @@ hipError_t launch_deferred_t(const DeferredArgs &a, hipStream_t st)
 // loads issued before the stores.
 constexpr int kStageVec = 4;
 constexpr int kStageUnroll = 4;
-constexpr int64_t kStageMaxChannels = (int64_t)1 << 28; // (tile_div; their state would exceed 500 GB)
+constexpr int64_t kStageMaxChannels = (int64_t)1 << 28; // (stage_row; their state would exceed 300 GB)
 
 // The sample is read once, and its ring row is read again only by the fold
 // of its subset: in the same push for one subset in T, up to T pushes (and
@@ -660,20 +660,27 @@ typedef float stage_f4 __attribute__((ext_vector_type(4)));
 
 // Vectors of a tile of the stage kernels: vector v lies in tile v / d at
 // vector v % d, d = tw / kStageVec (16 .. 1024), by a multiplication (exact for
-// v (d - 1) < 2^36, v < 2^31: launch_stage checks n_ch < 2^28).  With a 64-bit
+// v (d - 1) < 2^36, v < 2^31: the launchers check n_ch < 2^28).  With a 64-bit
 // division a vector (most of the kernel's instructions) a push of 250047, 3e6
 // and 1.2e7 channels took 3.2, 7.2 and 20.6 us instead of 3.0, 6.7 and 19.8
 // (4.8 TB/s).
-struct TileDiv {
+// Only what the kernels need is passed: a launch costs the host more with a
+// larger argument, and small groups are bound by their launches.
+struct StageArgs {
+    const float *samples;
+    char *state;
+    int64_t n_ch, tile_bytes;
+    StepRef step;
+    int32_t tw, p0;
     uint64_t mul; // ceil(2^36 / d)
     uint32_t d;
-    uint32_t pad_;
+    int32_t aligned;
 };
 
-__device__ __forceinline__ float *stage_row(const GroupArgs &g, const TileDiv &td, uint32_t v, int slot)
+__device__ __forceinline__ float *stage_row(const StageArgs &g, uint32_t v, int slot)
 {
-    const uint32_t tile = (uint32_t)((v * td.mul) >> 36);
-    const uint32_t lane = (v - tile * td.d) * kStageVec;
+    const uint32_t tile = (uint32_t)((v * g.mul) >> 36);
+    const uint32_t lane = (v - tile * g.d) * kStageVec;
     return reinterpret_cast<float *>(g.state + tile * g.tile_bytes) + (size_t)slot * g.tw + lane;
 }
 
@@ -689,21 +696,20 @@ __device__ __forceinline__ stage_f4 stage_load(const float *src, int64_t n, uint
     return x;
 }
 
-__global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, TileDiv td, int aligned)
+__global__ __launch_bounds__(256) void stage_kernel(StageArgs g)
 {
-    const int slot = slot_of(pushes_before(step), g.p0);
-    const float *src = static_cast<const float *>(g.samples);
+    const int slot = slot_of(pushes_before(g.step), g.p0);
     const uint32_t nvec = (uint32_t)((g.n_ch + kStageVec - 1) / kStageVec);
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t v0 = blockIdx.x * blockDim.x + threadIdx.x; v0 < nvec; v0 += stride * kStageUnroll) {
         stage_f4 x[kStageUnroll];
 #pragma unroll
         for (int u = 0; u < kStageUnroll; ++u)
-            if (v0 + u * stride < nvec) x[u] = stage_load(src, g.n_ch, v0 + u * stride, aligned);
+            if (v0 + u * stride < nvec) x[u] = stage_load(g.samples, g.n_ch, v0 + u * stride, g.aligned);
 #pragma unroll
         for (int u = 0; u < kStageUnroll; ++u)
             if (v0 + u * stride < nvec)
-                __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(stage_row(g, td, v0 + u * stride, slot)));
+                __builtin_nontemporal_store(x[u], reinterpret_cast<stage_f4 *>(stage_row(g, v0 + u * stride, slot)));
     }
 }
 
@@ -712,11 +718,10 @@ __global__ __launch_bounds__(256) void stage_kernel(GroupArgs g, StepRef step, T
 // rows are neighbours in the tile; blockIdx.y counts the row quads.
 // 244 pushes of 900000 channels take 321 us (5.5 TB/s) instead of 4.4 us each
 // (1.6 TB/s) as launches of their own.
-__global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef step, TileDiv td, int64_t pitch,
-                                                          int n_rows, int aligned)
+__global__ __launch_bounds__(256) void stage_rows_kernel(StageArgs g, int64_t pitch, int n_rows)
 {
     const int r0 = (int)blockIdx.y * kStageUnroll;
-    const int slot0 = slot_of(pushes_before(step) + r0, g.p0);
+    const int slot0 = slot_of(pushes_before(g.step) + r0, g.p0);
     const uint32_t nvec = (uint32_t)((g.n_ch + kStageVec - 1) / kStageVec);
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
@@ -724,9 +729,9 @@ __global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef st
 #pragma unroll
         for (int u = 0; u < kStageUnroll; ++u)
             if (r0 + u < n_rows)
-                x[u] = stage_load(reinterpret_cast<const float *>(static_cast<const char *>(g.samples) + (r0 + u) * pitch),
-                                  g.n_ch, v, aligned);
-        float *row = stage_row(g, td, v, 0);
+                x[u] = stage_load(reinterpret_cast<const float *>(reinterpret_cast<const char *>(g.samples) + (r0 + u) * pitch),
+                                  g.n_ch, v, g.aligned);
+        float *row = stage_row(g, v, 0);
 #pragma unroll
         for (int u = 0; u < kStageUnroll; ++u) {
             if (r0 + u >= n_rows) continue;
@@ -737,37 +742,46 @@ __global__ __launch_bounds__(256) void stage_rows_kernel(GroupArgs g, StepRef st
     }
 }
 
-TileDiv tile_div(const GroupArgs &g)
+// (pitch: of several rows; 16-byte vectors need aligned sources)
+StageArgs stage_args(const GroupArgs &g, StepRef step, int64_t pitch)
 {
-    const uint32_t d = (uint32_t)g.tw / kStageVec;
-    return TileDiv{(((uint64_t)1 << 36) + d - 1) / d, d, 0};
+    StageArgs a;
+    a.samples = static_cast<const float *>(g.samples);
+    a.state = g.state;
+    a.n_ch = g.n_ch;
+    a.tile_bytes = g.tile_bytes;
+    a.step = step;
+    a.tw = g.tw;
+    a.p0 = g.p0;
+    a.d = (uint32_t)g.tw / kStageVec;
+    a.mul = (((uint64_t)1 << 36) + a.d - 1) / a.d;
+    a.aligned = ((uintptr_t)g.samples % 16) == 0 && pitch % 16 == 0;
+    return a;
+}
+
+unsigned stage_blocks(const GroupArgs &g)
+{
+    const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
+    const int64_t blocks = (nvec + 255) / 256;
+    return (unsigned)(blocks > 2048 ? 2048 : blocks);
 }
 
 } // namespace
 
+// (single-precision samples only: the deferred form's kinds)
 hipError_t launch_stage(const GroupArgs &g, StepRef step, hipStream_t st)
 {
-    // single-precision samples only (the deferred form's kinds); 16-byte
-    // vectors need a 16-byte aligned source
     if (g.n_ch >= kStageMaxChannels) return hipErrorInvalidValue;
-    const int aligned = ((uintptr_t)g.samples % 16) == 0;
-    const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
-    int64_t blocks = (nvec + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g, step, tile_div(g), aligned);
+    hipLaunchKernelGGL(stage_kernel, dim3(stage_blocks(g)), dim3(256), 0, st, stage_args(g, step, 0));
     return hipGetLastError();
 }
 
 hipError_t launch_stage_rows(const GroupArgs &g, StepRef step, int64_t pitch, int n_rows, hipStream_t st)
 {
     if (n_rows < 1 || n_rows > g.p0 || g.n_ch >= kStageMaxChannels) return hipErrorInvalidValue;
-    const int aligned = ((uintptr_t)g.samples % 16) == 0 && pitch % 16 == 0;
-    const int64_t nvec = (g.n_ch + kStageVec - 1) / kStageVec;
-    int64_t blocks = (nvec + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
     const unsigned quads = (unsigned)((n_rows + kStageUnroll - 1) / kStageUnroll);
-    hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)blocks, quads), dim3(256), 0, st, g, step, tile_div(g),
-                       pitch, n_rows, aligned);
+    hipLaunchKernelGGL(stage_rows_kernel, dim3(stage_blocks(g), quads), dim3(256), 0, st,
+                       stage_args(g, step, pitch), pitch, n_rows);
     return hipGetLastError();
 }
 

@@ -199,7 +199,7 @@ struct KeepRow {
     int64_t wide; // both ends 16-byte aligned (set by the launcher)
 };
 struct KeepArgs {
-    KeepRow row[kMaxGroups];
+    KeepRow row[kMaxGroups]; // n of them set
     int32_t n;
     int32_t pad_;
 };

@@ -21,7 +21,7 @@ bool multi_supported(int kind, int p, int m, bool pair);
 // rows + s stride.
 hipError_t launch_multi_push(const GroupArgs &g, StepRef step, const void *rows, int64_t stride, int n,
                              hipStream_t st);
-hipError_t launch_keep_rows(const KeepArgs &a, hipStream_t st);
+hipError_t launch_keep_rows(KeepArgs &a, hipStream_t st); // (sets row[i].wide)
 hipError_t launch_push_end(const PushEndArgs &a, hipStream_t st); // flush records + step counter
 hipError_t launch_rhok(const RhokArgs &a, hipStream_t st);
 int rhok_tile_atoms(int nmax);

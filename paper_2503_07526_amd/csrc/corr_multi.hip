@@ -278,12 +278,11 @@ hipError_t launch_multi_pair(const GroupArgs &g, StepRef step, const void *rows,
     }
 }
 
-// Copy of this push's samples of up to kMaxGroups groups to their waiting rows
-// (blockIdx.y: the group): 16-byte words where both ends are aligned, else
-// 4-byte ones (every sample type is a multiple of 4 bytes).
-__global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a)
+// Copy of a push's samples of a group to its waiting row: 16-byte words where
+// both ends are aligned, else 4-byte ones (every sample type is a multiple of
+// 4 bytes).
+__device__ __forceinline__ void keep_row(const KeepRow &k)
 {
-    const KeepRow k = a.row[blockIdx.y];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k.wide) {
@@ -299,6 +298,12 @@ __global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a)
         for (int64_t i = i0; i < k.bytes / 4; i += stride) d[i] = s[i];
     }
 }
+
+// One group, or several (blockIdx.y: the group).  The push of a small group is
+// mostly the host's launch, and that grows with the argument: 2.8 us for one
+// row, 3.4 for the room of eight.
+__global__ __launch_bounds__(256) void keep_row_kernel(KeepRow k) { keep_row(k); }
+__global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a) { keep_row(a.row[blockIdx.y]); }
 
 } // namespace
 
@@ -316,19 +321,21 @@ hipError_t launch_multi_push(const GroupArgs &g, StepRef step, const void *rows,
                   : launch_multi_pair<false>(g, step, rows, stride, n, st);
 }
 
-hipError_t launch_keep_rows(const KeepArgs &a, hipStream_t st)
+hipError_t launch_keep_rows(KeepArgs &a, hipStream_t st)
 {
     if (a.n < 1 || a.n > kMaxGroups) return hipErrorInvalidValue;
-    KeepArgs b = a;
     int64_t most = 0;
-    for (int i = 0; i < b.n; ++i) {
-        KeepRow &k = b.row[i];
+    for (int i = 0; i < a.n; ++i) {
+        KeepRow &k = a.row[i];
         k.wide = (reinterpret_cast<uintptr_t>(k.src) | reinterpret_cast<uintptr_t>(k.dst)) % 16 == 0;
         most = k.bytes > most ? k.bytes : most;
     }
     int64_t blocks = (most / 16 + 255) / 256;
     blocks = blocks < 1 ? 1 : blocks > 2048 ? 2048 : blocks;
-    hipLaunchKernelGGL(keep_rows_kernel, dim3((unsigned)blocks, (unsigned)b.n), dim3(256), 0, st, b);
+    if (a.n == 1)
+        hipLaunchKernelGGL(keep_row_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a.row[0]);
+    else
+        hipLaunchKernelGGL(keep_rows_kernel, dim3((unsigned)blocks, (unsigned)a.n), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

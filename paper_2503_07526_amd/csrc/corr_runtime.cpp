@@ -694,7 +694,8 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     const size_t ng = c->groups.size();
     std::vector<const void *> resolved(ng);
     std::vector<void *> made(ng, nullptr); // where the producers write
-    KeepArgs keep{};
+    KeepArgs keep;
+    keep.n = 0;
     for (size_t i = 0; i < ng; ++i) {
         const Group &g = c->groups[i];
         // (the samples of a captured run stay where they are: its passes read them there)
