@@ -173,13 +173,14 @@ struct DeferredArgs {
                             // (row r at r - row_begin)
     double *slice_out;      // readout: [(c - slice_begin) * ne + e]
     FoldStamps *stamps;     // scheduled flush with timing: block start / end stamps, else null
-    // Fold straight from a stored history (fixed_group -2): row i (push
-    // T (fixed_block - 1) + 1 + i) of the block holds the n_ch samples at
-    // hist + i hist_stride bytes; null: the level-0 ring
+    // Fold straight from a stored history (fixed_group -2): row i >= hist_from
+    // (push T (fixed_block - 1) + 1 + i) of the block holds the n_ch samples at
+    // hist + i hist_stride bytes, the rows before are staged in the level-0 ring;
+    // null: all are
     const char *hist;
     int64_t hist_stride;
+    int32_t hist_from;
     int32_t threads;        // threads per block of the fold kernel (64, 128 or 256)
-    int32_t pad_;
 };
 
 struct PushArgs {

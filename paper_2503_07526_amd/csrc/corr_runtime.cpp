@@ -1690,49 +1690,53 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
     int32_t r = 0;
     const int T = ctx->defer_t;
     if (!ctx->deferred_set.empty() && n_steps >= T) {
-        // Block-deferred groups fold whole blocks of the history directly.
-        // Up to the next block boundary the pushes are staged.
-        if (ctx->n_push % T != 0) {
-            const int32_t n = (int32_t)std::min<int64_t>(n_steps, T - ctx->n_push % T);
+        // Block-deferred groups fold whole blocks of the history directly, and
+        // the block that is under way from its staged pushes and the history's
+        // (timed contexts stage up to the next block).
+        const bool others = !ctx->main_set.empty() || !ctx->side_set.empty();
+        if (ctx->counted && ctx->n_push % T != 0) {
+            const int32_t n = (int32_t)(T - ctx->n_push % T);
             int rc = some_pushes(0, n);
             if (rc != CORR_OK) return rc;
             r = n;
         }
-        const bool others = !ctx->main_set.empty() || !ctx->side_set.empty();
-        int64_t q = ctx->n_push / T; // blocks that end at or before the current push
-        bool behind = false;          // some tile group has not folded block q yet
-        for (int i : ctx->deferred_set)
-            for (int64_t f : ctx->groups[(size_t)i].flushed) behind = behind || f < q;
-        if (n_steps - r >= T && q >= 1 && behind) {
-            // every tile group folds block q now (their scheduled folds would
-            // come during the next T - 1 pushes)
-            int rc = fold_all(ctx, ctx->deferred_set, q);
-            if (rc != CORR_OK) return rc;
-        }
-        while (n_steps - r >= T) {
-            // the other groups' pushes of the block
+        while (n_steps - r >= T - ctx->n_push % T) {
+            const int64_t q = ctx->n_push / T;           // blocks completed
+            const int32_t from = (int32_t)(ctx->n_push % T); // pushes staged of the next
+            const int32_t n = T - from;
+            bool behind = false; // some tile group has not folded block q yet
+            for (int i : ctx->deferred_set)
+                for (int64_t f : ctx->groups[(size_t)i].flushed) behind = behind || f < q;
+            if (q >= 1 && behind) {
+                // every tile group folds block q now (their scheduled folds
+                // would come during the next T - 1 pushes)
+                int rc = fold_all(ctx, ctx->deferred_set, q);
+                if (rc != CORR_OK) return rc;
+            }
+            // the other groups' pushes
             if (others) {
-                int rc = other_pushes(r, T);
+                int rc = other_pushes(r, n);
                 if (rc != CORR_OK) return rc;
             }
             // block q + 1 of every block-deferred group, read from the history
+            // (row `from` of the block is row r)
             for (int i : ctx->deferred_set) {
                 DeferredArgs da = deferred_args(ctx, i);
                 da.fixed_group = -2;
                 da.fixed_block = q + 1;
                 da.tile_first = 0;
                 da.tile_end = da.g.n_tiles;
-                da.hist = static_cast<const char *>(samples[(size_t)i]) + (int64_t)r * stride[(size_t)i];
+                da.hist = static_cast<const char *>(samples[(size_t)i]) + (int64_t)(r - from) * stride[(size_t)i];
+                da.hist_from = from;
                 da.hist_stride = stride[(size_t)i];
                 da.stamps = ctx->d_stamps;
                 HIP_TRY(ctx, launch_history_fold(da, ctx->stream));
             }
             // (the other groups' pushes advanced the counter)
-            int rc = commit_block(ctx, ctx->deferred_set, q + 1, others ? 0 : T, true);
+            int rc = commit_block(ctx, ctx->deferred_set, q + 1, others ? 0 : n, true);
             if (rc != CORR_OK) return rc;
-            q += 1;
-            r += T;
-            if (!others) ctx->n_push += T;
+            r += n;
+            if (!others) ctx->n_push += n;
         }
     }
     while (r < n_steps) {
