@@ -10,6 +10,28 @@
 
 namespace corr {
 
+// n consecutive (new, lagged) value pairs of a ring of p0 slots in order, eight
+// loaded ahead of their products (one pair after the other the sums of 1536
+// complex channels at p = 4096 took 113 us instead of 58).
+template <typename S, typename F>
+__device__ __forceinline__ void pending_products(const S *ring, int tw, int p0, int sx, int sy, int n, F &&add)
+{
+    constexpr int U = 8;
+    for (int i = 0; i < n; i += U) {
+        S x[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = ring[(size_t)sx * tw]; // (past n: read, not used)
+            y[u] = ring[(size_t)sy * tw];
+            sx = sx + 1 == p0 ? 0 : sx + 1;
+            sy = sy + 1 == p0 ? 0 : sy + 1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u < n) add(x[u], y[u]);
+    }
+}
+
 // Products of the pushes that a one-level window in the block-deferred form
 // (corr_window.hip) has staged but not yet folded into lag L = e: its lag
 // block j = L / wlpb has folded every block q with kWindowT q + j <= S, so the
@@ -32,21 +54,14 @@ __device__ double2 window_pending(const ReduceArgs &a, int e, int64_t c)
     double re = 0.0, im = 0.0;
     if (a.kind >= K_CF32_F64) {
         const float2 *ring = reinterpret_cast<const float2 *>(tb) + lane;
-        for (int64_t s = s1; s <= S; ++s) {
-            const float2 x = ring[(size_t)sx * a.tw];
-            const float2 y = ring[(size_t)sy * a.tw];
+        pending_products(ring, a.tw, p0, sx, sy, (int)(S - s1 + 1), [&](float2 x, float2 y) {
             re += (double)x.x * (double)y.x + (double)x.y * (double)y.y;
             im += (double)x.y * (double)y.x - (double)x.x * (double)y.y;
-            sx = sx + 1 == p0 ? 0 : sx + 1;
-            sy = sy + 1 == p0 ? 0 : sy + 1;
-        }
+        });
     } else {
         const float *ring = reinterpret_cast<const float *>(tb) + lane;
-        for (int64_t s = s1; s <= S; ++s) {
-            re += (double)ring[(size_t)sx * a.tw] * (double)ring[(size_t)sy * a.tw];
-            sx = sx + 1 == p0 ? 0 : sx + 1;
-            sy = sy + 1 == p0 ? 0 : sy + 1;
-        }
+        pending_products(ring, a.tw, p0, sx, sy, (int)(S - s1 + 1),
+                         [&](float x, float y) { re += (double)x * (double)y; });
     }
     return make_double2(re, im);
 }
