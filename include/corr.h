@@ -255,14 +255,21 @@ int corr_push(corr_ctx *ctx, const void *const *samples);
  * Work is issued on the context's stream; the rows must stay valid until it
  * has run.
  *  - Without CORR_FLAG_GRAPH, the block-deferred groups fold every whole
- *    block of T pushes that the history holds (after the pushes up to the
- *    next block boundary, which are single pushes) in one pass per block,
- *    reading the block's samples from the history instead of staging them
- *    (the fold's products, block means and sums are the same); the other
- *    groups are pushed row by row.
+ *    block of T pushes that the history holds (and the block under way, from
+ *    its staged pushes and the history's) in one pass per block, reading the
+ *    samples from the history instead of staging them (the fold's products,
+ *    block means and sums are the same); the other rows are staged together,
+ *    and the folds scheduled for them follow in one launch (with
+ *    CORR_FLAG_TIMING row by row).  Sample groups with multi-step passes (see
+ *    corr_kernel_time's notes on the forms) read the history directly where no
+ *    other group needs a launch per push; the other groups are pushed row by
+ *    row.
  *  - With CORR_FLAG_GRAPH, the n_steps single pushes are captured once as a
  *    graph and replayed; the few most recent (histories, strides, n_steps)
  *    keep their graphs, so repeated replays of the same buffers launch once.
+ *    Up to 64 pushes end together inside the graph (multi-step passes for the
+ *    groups that have them; one end kernel per stream, with
+ *    CORR_FLAG_TIMING one per push).
  *    No timing events are recorded in these replays (the fold kernels' device
  *    stamps are kept). */
 int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
@@ -377,6 +384,16 @@ int corr_state_bytes(const corr_ctx *ctx, int32_t group, int64_t *bytes);
  * floating-point sums differs.  A readout first folds complete blocks a
  * subset has not folded yet (exactly what its scheduled flush would do), then
  * folds the pushes after the last block without modifying state.
+ *
+ * Multi-step passes of the per-step form: groups with m = 2 and 16, 24 or 32
+ * points (any dtype and accumulator, pair groups except complex double) let up
+ * to 64 pushes wait in rows outside the state (64 times the push's bytes of
+ * device memory, at most a sixteenth of what is free when the context is
+ * created; groups beyond that push step by step) and add them in one pass,
+ * with the operations of single pushes in their order: the same results bit
+ * for bit.  A readout adds the waiting pushes first.  Not with
+ * CORR_FLAG_DIRECT or CORR_FLAG_PER_GROUP; with CORR_FLAG_GRAPH inside
+ * corr_push_steps only; not with CORR_FLAG_TIMING alone.
  *
  * Block-deferred window: a group with one level (b = 1), p >= 512 points and
  * single-precision samples (real or complex, any accumulator; not pair
