@@ -191,20 +191,6 @@ struct PushArgs {
     StepRef step;        // pushes completed before this one
 };
 
-// One push's samples of a group, copied to a row where they wait for a
-// multi-step pass.
-struct KeepRow {
-    const void *src;
-    void *dst;
-    int64_t bytes;
-    int64_t wide; // both ends 16-byte aligned (set by the launcher)
-};
-struct KeepArgs {
-    KeepRow row[kMaxGroups]; // n of them set
-    int32_t n;
-    int32_t pad_;
-};
-
 // Number of accumulator planes of a kind (2 for compensated sums).
 inline int acc_planes(int kind) { return (kind == K_F32_KAHAN || kind == K_CF32_KAHAN) ? 2 : 1; }
 inline bool kind_complex(int kind) { return kind >= K_CF32_F64; }
@@ -225,6 +211,25 @@ inline int kind_acc_bytes(int kind)
     default: return 8; // complex float planes
     }
 }
+
+// One push's samples of a group, copied to a row where they wait for a
+// multi-step pass.
+struct KeepRow {
+    const void *src;
+    void *dst;
+    int64_t bytes;
+    int64_t wide; // both ends 16-byte aligned (set by the launcher)
+};
+// A small group's copy may ride on a producer's final kernel (an extra block)
+// instead of a launch of its own: 32 pushes of the momentum densities of 5e6
+// atoms beside a 3-channel group, and a readout, 704 us instead of 755.
+constexpr int64_t kRiderBytes = 16 << 10;
+
+struct KeepArgs {
+    KeepRow row[kMaxGroups]; // n of them set
+    int32_t n;
+    int32_t pad_;
+};
 
 // k-density producer: k-vectors are grouped in segments of up to kSegWidth
 // vectors sharing (n_y, n_z) with n_x in [nx0, nx0 + kSegWidth).

@@ -26,10 +26,11 @@ hipError_t launch_push_end(const PushEndArgs &a, hipStream_t st); // flush recor
 hipError_t launch_rhok(const RhokArgs &a, hipStream_t st);
 int rhok_tile_atoms(int nmax);
 int rhok_block_threads(int n_seg);
-hipError_t launch_rhok_mfma(const RhokMfmaArgs &a, hipStream_t st);
+// (rider: a copy of the final kernel's extra block; bytes 0: none)
+hipError_t launch_rhok_mfma(const RhokMfmaArgs &a, const KeepRow &rider, hipStream_t st);
 int rhok_mfma_cols();        // |n_z| columns of the matrix-core producer
 int rhok_mfma_max_nmax();    // largest |n component| it takes
-hipError_t launch_momentum(const MomentumArgs &a, hipStream_t st); // partial + final kernels
+hipError_t launch_momentum(const MomentumArgs &a, const KeepRow &rider, hipStream_t st); // partial + final kernels
 int momentum_blocks(int64_t n_atoms); // blocks of the partial kernel (size of the partial buffer)
 hipError_t rhok_mfma_prepare(int table_rows, int nw, int nmax); // once per context, before the first launch
 int rhok_mfma_chunks(int n_mtiles, int nw); // blocks along the M tiles (grid.x)

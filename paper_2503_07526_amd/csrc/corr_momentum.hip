@@ -12,6 +12,7 @@
 // not depend on timing.
 #include <hip/hip_runtime.h>
 
+#include "corr_keep.h"
 #include "corr_kernels.h"
 #include "corr_wave.h"
 
@@ -117,11 +118,15 @@ template <typename T> __global__ __launch_bounds__(kMomThreads) void momentum_pa
 // One wave per channel (block q): lane l adds the block sums l, l + 64, ...
 // in order (at most kMomMaxBlocks / 64, all loaded first), then the wave adds
 // its lanes in a fixed order.
-template <typename T> __global__ __launch_bounds__(64) void momentum_final_kernel(MomentumArgs a)
+template <typename T> __global__ __launch_bounds__(64) void momentum_final_kernel(MomentumArgs a, KeepRow rider)
 {
     const int q = blockIdx.x;
     const int nch = 3 * a.n_species;
     const int lane = threadIdx.x;
+    if (q == nch) { // the rider's block
+        keep_row(rider, lane, 64);
+        return;
+    }
     constexpr int N = kMomMaxBlocks / 64;
     double v[N], x = 0.0;
 #pragma unroll
@@ -161,7 +166,7 @@ int momentum_blocks(int64_t n_atoms)
     return (int)b;
 }
 
-hipError_t launch_momentum(const MomentumArgs &a, hipStream_t st)
+hipError_t launch_momentum(const MomentumArgs &a, const KeepRow &rider, hipStream_t st)
 {
     if (a.n_species < 1 || a.n_species > kMomMaxSpecies || a.n_atoms < 1 || a.n_blocks < 1 ||
         a.n_blocks > kMomMaxBlocks)
@@ -175,11 +180,11 @@ hipError_t launch_momentum(const MomentumArgs &a, hipStream_t st)
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)(3 * a.n_species));
+    const dim3 grid((unsigned)(3 * a.n_species + (rider.bytes > 0 ? 1 : 0)));
     if (a.dbl)
-        hipLaunchKernelGGL(momentum_final_kernel<double>, grid, dim3(64), 0, st, a);
+        hipLaunchKernelGGL(momentum_final_kernel<double>, grid, dim3(64), 0, st, a, rider);
     else
-        hipLaunchKernelGGL(momentum_final_kernel<float>, grid, dim3(64), 0, st, a);
+        hipLaunchKernelGGL(momentum_final_kernel<float>, grid, dim3(64), 0, st, a, rider);
     return hipGetLastError();
 }
 

@@ -24,6 +24,7 @@
 // and 20 levels: 13 us against 64 x 4).
 #include <hip/hip_runtime.h>
 
+#include "corr_keep.h"
 #include "corr_kernels.h"
 #include "corr_sums.h"
 
@@ -278,32 +279,17 @@ hipError_t launch_multi_pair(const GroupArgs &g, StepRef step, const void *rows,
     }
 }
 
-// Copy of a push's samples of a group to its waiting row: 16-byte words where
-// both ends are aligned, else 4-byte ones (every sample type is a multiple of
-// 4 bytes).
-__device__ __forceinline__ void keep_row(const KeepRow &k)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k.wide) {
-        const uint4 *s = static_cast<const uint4 *>(k.src);
-        uint4 *d = static_cast<uint4 *>(k.dst);
-        const int64_t n = k.bytes / 16;
-        for (int64_t i = i0; i < n; i += stride) d[i] = s[i];
-        const int64_t t = n * 4 + i0; // the last 0 .. 3 words
-        if (t < k.bytes / 4) static_cast<uint32_t *>(k.dst)[t] = static_cast<const uint32_t *>(k.src)[t];
-    } else {
-        const uint32_t *s = static_cast<const uint32_t *>(k.src);
-        uint32_t *d = static_cast<uint32_t *>(k.dst);
-        for (int64_t i = i0; i < k.bytes / 4; i += stride) d[i] = s[i];
-    }
-}
-
 // One group, or several (blockIdx.y: the group).  The push of a small group is
 // mostly the host's launch, and that grows with the argument: 2.8 us for one
 // row, 3.4 for the room of eight.
-__global__ __launch_bounds__(256) void keep_row_kernel(KeepRow k) { keep_row(k); }
-__global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a) { keep_row(a.row[blockIdx.y]); }
+__global__ __launch_bounds__(256) void keep_row_kernel(KeepRow k)
+{
+    keep_row(k, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
+__global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a)
+{
+    keep_row(a.row[blockIdx.y], (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
 
 } // namespace
 
@@ -327,7 +313,7 @@ hipError_t launch_keep_rows(KeepArgs &a, hipStream_t st)
     int64_t most = 0;
     for (int i = 0; i < a.n; ++i) {
         KeepRow &k = a.row[i];
-        k.wide = (reinterpret_cast<uintptr_t>(k.src) | reinterpret_cast<uintptr_t>(k.dst)) % 16 == 0;
+        k.wide = keep_wide(k);
         most = k.bytes > most ? k.bytes : most;
     }
     int64_t blocks = (most / 16 + 255) / 256;

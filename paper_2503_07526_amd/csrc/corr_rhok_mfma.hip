@@ -48,6 +48,7 @@
 // forms fewer products per pair on the vector units.
 #include <hip/hip_runtime.h>
 
+#include "corr_keep.h"
 #include "corr_kernels.h"
 #include "corr_wave.h"
 
@@ -1048,8 +1049,7 @@ void rhok_couple_kernel(RhokMfmaArgs a)
 // four blocks ahead of their additions, and the 2 NW sums over the lanes share
 // their exchanges (currents of 2048 k-vectors 6.2 -> 4.8 us, of 512 7.3 -> 4.7;
 // n(k) of 300 3.3 -> 2.5).
-template <int NW>
-__global__ __launch_bounds__(256) void rhok_mfma_final_kernel(RhokMfmaArgs a)
+template <int NW> __device__ __forceinline__ void rhok_mfma_final(const RhokMfmaArgs &a)
 {
     const int k = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -1115,6 +1115,32 @@ __global__ __launch_bounds__(256) void rhok_mfma_final_kernel(RhokMfmaArgs a)
         else
             static_cast<float2 *>(a.out)[3 * k + lane] = make_float2((float)r, (float)i);
     }
+}
+
+template <int NW> __global__ __launch_bounds__(256) void rhok_mfma_final_kernel(RhokMfmaArgs a)
+{
+    rhok_mfma_final<NW>(a);
+}
+
+// With a small group's copy in the last block (a kernel of its own: the
+// argument of a launch costs the host time).
+template <int NW>
+__global__ __launch_bounds__(256) void rhok_mfma_final_rider_kernel(RhokMfmaArgs a, KeepRow rider)
+{
+    if (blockIdx.x == gridDim.x - 1)
+        keep_row(rider, threadIdx.x, blockDim.x);
+    else
+        rhok_mfma_final<NW>(a);
+}
+
+template <int NW> hipError_t launch_final(const RhokMfmaArgs &a, const KeepRow &rider, hipStream_t st)
+{
+    const unsigned blocks = (unsigned)((a.nk + 3) / 4);
+    if (rider.bytes > 0)
+        hipLaunchKernelGGL(rhok_mfma_final_rider_kernel<NW>, dim3(blocks + 1), dim3(256), 0, st, a, rider);
+    else
+        hipLaunchKernelGGL(rhok_mfma_final_kernel<NW>, dim3(blocks), dim3(256), 0, st, a);
+    return hipGetLastError();
 }
 
 } // namespace
@@ -1211,7 +1237,7 @@ int rhok_mfma_blocks_per_cu(int n_mtiles, int nw, int table_rows)
     return nw == 1 && couple_cwaves(n_mtiles) + 1 <= 8 && 2 * couple_lds_bytes(table_rows) <= kLdsBytes ? 2 : 1;
 }
 
-static hipError_t launch_couples(const RhokMfmaArgs &a, hipStream_t st)
+static hipError_t launch_couples(const RhokMfmaArgs &a, const KeepRow &rider, hipStream_t st)
 {
     const int chunks = rhok_mfma_chunks(a.n_mtiles, 1);
     const int cwaves = couple_cwaves(a.n_mtiles);
@@ -1224,12 +1250,10 @@ static hipError_t launch_couples(const RhokMfmaArgs &a, hipStream_t st)
                            dim3((cwaves + 1) * 64), lds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rhok_mfma_final_kernel<1>, dim3((unsigned)((a.nk + 3) / 4)), dim3(256), 0, st,
-                       a);
-    return hipGetLastError();
+    return launch_final<1>(a, rider, st);
 }
 
-template <int TA, int NB> static hipError_t launch_currents(const RhokMfmaArgs &a, hipStream_t st)
+template <int TA, int NB> static hipError_t launch_currents(const RhokMfmaArgs &a, const KeepRow &rider, hipStream_t st)
 {
     // waves per block: the M tiles dealt evenly over the fewest blocks, at
     // least one thread per table task
@@ -1241,25 +1265,23 @@ template <int TA, int NB> static hipError_t launch_currents(const RhokMfmaArgs &
                        dim3(waves * 64), lds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rhok_mfma_final_kernel<3>, dim3((unsigned)((a.nk + 3) / 4)), dim3(256), 0,
-                       st, a);
-    return hipGetLastError();
+    return launch_final<3>(a, rider, st);
 }
 
-hipError_t launch_rhok_mfma(const RhokMfmaArgs &a, hipStream_t st)
+hipError_t launch_rhok_mfma(const RhokMfmaArgs &a, const KeepRow &rider, hipStream_t st)
 {
     if (a.nmax > kMfmaCols - 1 || a.n_mtiles < 1 || a.x_rows < 1 || a.y_rows < 1 ||
         a.x_rows + a.y_rows > 4 * kMfmaCols - 2)
         return hipErrorInvalidValue;
     const int rows = a.x_rows + a.y_rows;
-    if (a.nw == 1) return launch_couples(a, st);
+    if (a.nw == 1) return launch_couples(a, rider, st);
     if (a.nw != 3) return hipErrorInvalidValue;
     const int nb = current_btiles(a.nmax);
     if (tile_atoms(rows, nb) == 128)
-        return nb == 1 ? launch_currents<128, 1>(a, st)
-               : nb == 2 ? launch_currents<128, 2>(a, st) : launch_currents<128, 3>(a, st);
-    return nb == 1 ? launch_currents<64, 1>(a, st)
-           : nb == 2 ? launch_currents<64, 2>(a, st) : launch_currents<64, 3>(a, st);
+        return nb == 1 ? launch_currents<128, 1>(a, rider, st)
+               : nb == 2 ? launch_currents<128, 2>(a, rider, st) : launch_currents<128, 3>(a, rider, st);
+    return nb == 1 ? launch_currents<64, 1>(a, rider, st)
+           : nb == 2 ? launch_currents<64, 2>(a, rider, st) : launch_currents<64, 3>(a, rider, st);
 }
 
 } // namespace corr

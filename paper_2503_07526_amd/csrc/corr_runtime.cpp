@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/corr.h"
+#include "corr_keep.h"
 #include "corr_kernels.h"
 #include "corr_tune.h"
 
@@ -731,8 +732,27 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         HIP_TRY(c, hipEventRecord(c->ev_fork, st));
         HIP_TRY(c, hipStreamWaitEvent(c->side_stream, c->ev_fork, 0));
     }
+    // The small copy that rides on the first producer's final kernel: a small
+    // block-deferred group's staging (one tile) or the first kept row, on one
+    // stream and where the host knows the ring slot.
+    KeepRow rider{};
+    int rider_group = -1;
+    if (!c->counted && !fork && !c->side_set.empty() &&
+        (c->groups[(size_t)c->side_set[0]].mom || c->groups[(size_t)c->side_set[0]].rhok_mfma)) {
+        for (int i : dset) {
+            const Group &g = c->groups[(size_t)i];
+            if (rider_group >= 0 || g.n_tiles != 1 || (int64_t)g.input_bytes > kRiderBytes) continue;
+            rider = KeepRow{src[i], g.state + (c->n_push % g.p0) * c->tuning.tile_channels * (int64_t)g.s_bytes,
+                            (int64_t)g.input_bytes, 0};
+            rider_group = i;
+        }
+        if (rider_group < 0 && keep.n > 0 && keep.row[keep.n - 1].bytes <= kRiderBytes)
+            rider = keep.row[--keep.n];
+        rider.wide = keep_wide(rider);
+    }
     if (keep.n > 0) HIP_TRY(c, launch_keep_rows(keep, st));
     for (int i : dset) {
+        if (i == rider_group) continue;
         GroupArgs ga = c->pargs.g[(size_t)i];
         ga.samples = resolved[(size_t)i];
         HIP_TRY(c, launch_stage(ga, step_main(c, run), st));
@@ -753,14 +773,14 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
             ma.vec4 = g.d.n_atoms % 4 == 0 && reinterpret_cast<uintptr_t>(src[i]) % 16 == 0;
             ma.out = made[(size_t)i];
             ma.stamps = pst_stamps;
-            HIP_TRY(c, launch_momentum(ma, pst));
+            HIP_TRY(c, launch_momentum(ma, i == c->side_set[0] ? rider : KeepRow{}, pst));
         } else if (g.rhok_mfma) {
             RhokMfmaArgs ma = g.margs;
             ma.pos = static_cast<const float *>(src[i]);
             ma.out = made[(size_t)i];
             ma.stamps = pst_stamps;
             ma.early_loads = fork && !chained ? 1 : 0; // beside the flush, joined every push
-            HIP_TRY(c, launch_rhok_mfma(ma, pst));
+            HIP_TRY(c, launch_rhok_mfma(ma, i == c->side_set[0] ? rider : KeepRow{}, pst));
         } else {
             RhokArgs ra = g.rargs;
             ra.pos = static_cast<const float *>(src[i]);

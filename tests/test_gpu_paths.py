@@ -283,3 +283,36 @@ def test_captured_runs(corrmod, overlap, timing, k):
                 for i, g in enumerate(groups):
                     kw = dict(slice_=(0, min(g.n_channels, 40)))
                     _same_readout(c.finalize(i, **kw), ref.finalize(i, **kw), f"[{b}, {e}) group {i}")
+
+
+@pytest.mark.parametrize("source", ["momentum", "rhok", "currents"])
+@pytest.mark.parametrize("n,dtype", [(1, "f32"), (3, "f32"), (512, "f32"), (513, "f32"), (9, "f64"), (2049, "f64")])
+def test_small_group_beside_a_producer(corrmod, source, n, dtype):
+    """A small sample group whose copy the producer's final kernel carries (one
+    tile of staging, a kept row of up to 16 KB; one channel more has its own
+    launch): the same bits as the group by itself, the producer's as by itself."""
+    N, box, S = 300, 20.0, 300
+    say(f"[rider] {source} n={n} {dtype}")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    t = torch.float32 if dtype == "f32" else torch.float64
+    flat = torch.randn((S * n + 1,), generator=gen, device="cuda", dtype=t)
+    small = flat[1:].reshape(S, n)  # rows that are not 16-byte aligned
+    d = corrmod.GroupDesc(n, 6, 16, 2, dtype=dtype, accum="kahan" if dtype == "f32" else "f64")
+    kv = synth.kvectors(20)
+    width = 6 if source == "currents" else 3
+    big = box * torch.rand((S, width * N), generator=gen, device="cuda")
+    if source == "momentum":
+        p = corrmod.GroupDesc(6, 6, 16, 2, dtype="f32", accum="kahan", source=source, n_atoms=N, box=box,
+                              species=np.arange(N, dtype=np.int32) % 2, masses=np.array([2.0, 3.0]))
+    else:
+        p = corrmod.GroupDesc(20 * width // 2 if source == "currents" else 20, 6, 32, 2, dtype="cf32", accum="kahan",
+                              source=source, kvec=kv, n_atoms=N, box=box)
+    with corrmod.Correlator([p, d]) as c, corrmod.Correlator([d]) as alone, corrmod.Correlator([p]) as prod:
+        for s in range(S):
+            c.push([big[s], small[s]])
+            alone.push([small[s]])
+            prod.push([big[s]])
+            if s in (0, 70, 256, S - 1):
+                kw = dict(slice_=(max(0, n - 4), n))
+                _same_readout(c.finalize(1, **kw), alone.finalize(0, **kw), f"S={s + 1}")
+                _same_readout(c.finalize(0, slice_=(0, 6)), prod.finalize(0, slice_=(0, 6)), f"S={s + 1} producer")
