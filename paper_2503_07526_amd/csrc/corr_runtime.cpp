@@ -79,6 +79,9 @@ struct Group {
     bool multi = false;
     char *rows = nullptr;
     int64_t row_bytes = 0;
+    // pushes after the last pass of every group that this group's sums hold
+    // already: 0, unless the pass of a group after it was refused
+    int32_t taken = 0;
     int64_t *d_flushed = nullptr;                // [kFlushGroups] blocks folded per tile group (T used)
     std::vector<int64_t> flushed;                // host mirror of d_flushed
     int64_t tiles_per_group = 0;
@@ -648,18 +651,33 @@ int launch_set(corr_ctx *c, const PushArgs &base, StepRef step, const std::vecto
     return CORR_OK;
 }
 
-// Groups with waiting pushes: add them (n_done: pushes issued, those
-// included).  On the context's stream.
-int add_waiting(corr_ctx *c, int64_t n_done)
+// Multi-step pass of every group over its next n pushes, those after the first
+// `before`: push r of them at rows(i) + r pitch(i).  On the context's stream.
+// Where the pass of a group is refused, the groups before it remember that
+// they hold these pushes, and a repeated call goes on with the others.
+template <typename Rows, typename Pitch>
+int add_pushes(corr_ctx *c, int64_t before, int32_t n, Rows &&rows, Pitch &&pitch)
+{
+    for (int i : c->multi_set) {
+        Group &g = c->groups[(size_t)i];
+        if (g.taken >= n) continue;
+        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{nullptr, before + g.taken}, rows(i) + g.taken * pitch(i),
+                                     pitch(i), n - g.taken, c->stream));
+        g.taken = n;
+    }
+    for (int i : c->multi_set) c->groups[(size_t)i].taken -= n;
+    return CORR_OK;
+}
+
+// Add the pushes that wait (the last ones counted).
+int add_waiting(corr_ctx *c)
 {
     if (c->waiting == 0) return CORR_OK;
-    for (int i : c->multi_set) {
-        const Group &g = c->groups[(size_t)i];
-        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{nullptr, n_done - c->waiting}, g.rows, g.row_bytes,
-                                     c->waiting, c->stream));
-    }
-    c->waiting = 0;
-    return CORR_OK;
+    const int rc = add_pushes(
+        c, c->n_push - c->waiting, c->waiting, [&](int i) -> const char * { return c->groups[(size_t)i].rows; },
+        [&](int i) { return c->groups[(size_t)i].row_bytes; });
+    if (rc == CORR_OK) c->waiting = 0;
+    return rc;
 }
 
 // Issue one push of every group on stream `st` with the given per-group
@@ -693,6 +711,10 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     const corr_ctx::Upd &upd = run ? c->upd_run : c->upd;
     const bool ends = !run || run->each; // the push has its own end kernel
     const size_t ng = c->groups.size();
+    if (c->waiting == kMultiT) { // no row is free: add the waiting pushes, or refuse this one
+        int rc = add_waiting(c);
+        if (rc != CORR_OK) return rc;
+    }
     std::vector<const void *> resolved(ng);
     std::vector<void *> made(ng, nullptr); // where the producers write
     KeepArgs keep;
@@ -842,10 +864,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     if (fork_updates) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     if (fork && !chained) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
-    if (!c->counted && !c->multi_set.empty() && ++c->waiting == kMultiT) {
-        int rc = add_waiting(c, c->n_push + 1);
-        if (rc != CORR_OK) return rc;
-    }
+    if (!c->counted && !c->multi_set.empty()) c->waiting += 1; // (nothing below can fail then)
     if (!c->counted || !ends) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
@@ -1653,15 +1672,18 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
     const bool each_push = ctx->counted || !ctx->side_set.empty() || !ctx->upd.main.empty();
     auto other_pushes = [&](int32_t r0, int32_t n) -> int {
         if (!each_push) {
-            int rc = add_waiting(ctx, ctx->n_push);
-            if (rc != CORR_OK) return rc;
-            for (int i : ctx->multi_set)
-                for (int32_t k = 0; k < n; k += kMultiT)
-                    HIP_TRY(ctx, launch_multi_push(ctx->pargs.g[i], StepRef{nullptr, ctx->n_push + k},
-                                                   static_cast<const char *>(samples[i]) + (int64_t)(r0 + k) * stride[(size_t)i],
-                                                   stride[(size_t)i], std::min(kMultiT, n - k), ctx->stream));
-            ctx->n_push += n;
-            return CORR_OK;
+            int rc = add_waiting(ctx);
+            for (int32_t k = 0; rc == CORR_OK && k < n; k += kMultiT) {
+                const int32_t m = std::min(kMultiT, n - k);
+                rc = add_pushes(
+                    ctx, ctx->n_push, m,
+                    [&](int i) {
+                        return static_cast<const char *>(samples[i]) + (int64_t)(r0 + k) * stride[(size_t)i];
+                    },
+                    [&](int i) { return stride[(size_t)i]; });
+                if (rc == CORR_OK) ctx->n_push += m;
+            }
+            return rc;
         }
         for (int32_t k = 0; k < n; ++k) {
             row(r0 + k);
@@ -1923,8 +1945,11 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         return set_err(ctx, CORR_E_INVALID, "Green-Kubo prefactor needs volume, kB, temperature > 0");
 
     {
-        int rc = add_waiting(ctx, ctx->n_push);
+        int rc = add_waiting(ctx);
         if (rc != CORR_OK) return rc;
+        if (g.taken > 0)
+            return set_err(ctx, CORR_E_STATE, "group %d holds pushes of a corr_push_steps call that failed: repeat it",
+                           group);
     }
     const int64_t S = ctx->n_push;
     const int tw = ctx->tuning.tile_channels;

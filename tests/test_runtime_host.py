@@ -1,0 +1,159 @@
+"""The library's host side on the CPU, its kernels replaced by a record of what
+they would add (tests/host_runtime.cpp): every push reaches a group's sums
+exactly once and in order, also after a launch that was refused."""
+import ctypes
+import os
+import subprocess
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def stub_path(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host") / "libcorr_host.so")
+    csrc = os.path.join(ROOT, "paper_2503_07526_amd", "csrc")
+    subprocess.check_call(
+        ["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+         "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=x", "-I/opt/rocm/include",
+         os.path.join(csrc, "corr_runtime.cpp"), os.path.join(csrc, "corr_autotune.cpp"),
+         os.path.join(ROOT, "tests", "host_runtime.cpp"), "-o", out])
+    return out
+
+
+class Host:
+    """The binding over the recording library."""
+
+    def __init__(self, corr):
+        self.corr, self.L = corr, corr.lib()
+        self.L.stub_reset()
+
+    def context(self, groups, **kw):
+        return self.corr.Correlator(groups, stream=SimpleNamespace(cuda_stream=0), **kw)
+
+    def fail(self, name, after=0):
+        self.L.stub_fail(name.encode(), after)
+
+    def calls(self, name):
+        return self.L.stub_calls(name.encode())
+
+    def added(self, n_ch):
+        """[(push number, its first sample)] added to the group of n_ch channels."""
+        push, value = (ctypes.c_int64 * 4096)(), (ctypes.c_float * 4096)()
+        n = self.L.stub_added(ctypes.c_int64(n_ch), push, value, 4096)
+        return list(zip(push[:n], value[:n]))
+
+
+@pytest.fixture
+def host(stub_path, monkeypatch):
+    import paper_2503_07526_amd.corr as c
+    monkeypatch.setattr(c, "_lib", None)
+    monkeypatch.setattr(c, "LIB_PATH", stub_path)
+    monkeypatch.setenv("CORR_TUNE_CACHE", "/nonexistent/none")
+    return Host(c)
+
+
+def _frames(steps, *channels):
+    """[steps][n] samples of every group; row s holds s + 1 everywhere."""
+    return [np.repeat(np.arange(1, steps + 1, dtype=np.float32)[:, None], n, 1) for n in channels]
+
+
+def _push(c, frames, s):
+    c.push([f[s].ctypes.data for f in frames])
+
+
+def _every_push_once(host, n_ch, steps):
+    assert host.added(n_ch) == [(s, float(s)) for s in range(1, steps + 1)], f"{n_ch} channels"
+
+
+@pytest.mark.parametrize("after", [0, 1])
+@pytest.mark.parametrize("retry", ["push", "finalize"])
+def test_refused_pass_of_waiting_pushes(host, after, retry):
+    """A pass that the runtime refuses, for the first or the second of two
+    groups, after 64 pushes or at a readout: the call that needed it fails, no
+    push is written past the rows, and after the next calls every push is in
+    the sums of both groups once."""
+    groups = [host.corr.GroupDesc(n, 3, 32, 2) for n in (5, 7)]
+    steps = 200
+    frames = _frames(steps, 5, 7)
+    with host.context(groups) as c:
+        s = refused = 0
+        if retry == "finalize":
+            for s in range(10):
+                _push(c, frames, s)
+            s = 10
+            host.fail("multi_push", after)
+            with pytest.raises(host.corr.CorrError):
+                c.finalize(0)
+            refused = 1
+        else:
+            host.fail("multi_push", after)
+        while s < steps:
+            try:
+                _push(c, frames, s)
+                s += 1
+            except host.corr.CorrError:
+                refused += 1
+                assert refused == 1
+            assert c.n_pushes() == s
+        c.finalize(0)
+        assert refused == 1 and host.L.stub_out_of_range() == 0
+        for n in (5, 7):
+            _every_push_once(host, n, steps)
+
+
+def test_passes_refused_several_times(host):
+    """Passes refused several times in a row: pushes fail while no row is free
+    and go on when the runtime takes launches again."""
+    g = host.corr.GroupDesc(6, 3, 32, 2)
+    frames = _frames(130, 6)
+    with host.context([g]) as c:
+        s = refused = 0
+        while s < 130:
+            if refused < 4:
+                host.fail("multi_push")
+            try:
+                _push(c, frames, s)
+                s += 1
+            except host.corr.CorrError:
+                refused += 1
+            assert c.n_pushes() == s
+        c.finalize(0)
+        assert refused == 4 and host.L.stub_out_of_range() == 0
+        _every_push_once(host, 6, 130)
+
+
+@pytest.mark.parametrize("after", [0, 4, 5])
+def test_refused_pass_of_a_history(host, after):
+    """A pass over the rows of a history refused, for the first or the second of
+    two groups: no readout of a group that is ahead of the count, and the rows
+    that were not counted, given again, are in the sums once."""
+    groups = [host.corr.GroupDesc(n, 3, 32, 2) for n in (5, 7)]
+    hist = _frames(300, 5, 7)
+    strides = (ctypes.c_int64 * 2)(*[h.strides[0] for h in hist])
+    with host.context(groups) as c:
+        for s in range(3):
+            _push(c, hist, s)
+
+        def steps(done):
+            rows = (ctypes.c_void_p * 2)(*[h[done:].ctypes.data for h in hist])
+            return host.L.corr_push_steps(c._h, 300 - done, rows, strides)
+
+        host.fail("multi_push", after)
+        assert steps(3) != 0
+        done = c.n_pushes()
+        assert done == (3 if after < 2 else 3 + 64)
+        if after == 5:
+            with pytest.raises(host.corr.CorrError):
+                c.finalize(0)
+        c.finalize(1)
+        if after == 4:
+            _push(c, hist, done)
+            done += 1
+        assert steps(done) == 0 and c.n_pushes() == 300
+        c.finalize(0)
+        for n in (5, 7):
+            _every_push_once(host, n, 300)
