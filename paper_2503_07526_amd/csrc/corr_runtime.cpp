@@ -232,6 +232,16 @@ int hip_err(corr_ctx *c, hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_err((ctx), e_, #expr);                                  \
     } while (0)
 
+// The launchers return hipGetLastError(), and with it an error that the
+// caller's own HIP calls left behind.  Such an error is reported here, before
+// anything is issued: reported by a launch that was made, it would have a
+// repeated call add the same pushes, or fold the same blocks, again.
+int pending_error(corr_ctx *c)
+{
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? CORR_OK : hip_err(c, e, "an earlier HIP call of this thread");
+}
+
 int kind_of(int dtype, int accum)
 {
     switch (dtype) {
@@ -711,6 +721,10 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     const corr_ctx::Upd &upd = run ? c->upd_run : c->upd;
     const bool ends = !run || run->each; // the push has its own end kernel
     const size_t ng = c->groups.size();
+    if (st == c->stream) {
+        int rc = pending_error(c);
+        if (rc != CORR_OK) return rc;
+    }
     if (c->waiting == kMultiT) { // no row is free: add the waiting pushes, or refuse this one
         int rc = add_waiting(c);
         if (rc != CORR_OK) return rc;
@@ -1729,6 +1743,10 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
         }
         return CORR_OK;
     };
+    {
+        int rc = pending_error(ctx);
+        if (rc != CORR_OK) return rc;
+    }
     int32_t r = 0;
     const int T = ctx->defer_t;
     if (!ctx->deferred_set.empty() && n_steps >= T) {
@@ -1945,7 +1963,8 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         return set_err(ctx, CORR_E_INVALID, "Green-Kubo prefactor needs volume, kB, temperature > 0");
 
     {
-        int rc = add_waiting(ctx);
+        int rc = pending_error(ctx);
+        if (rc == CORR_OK) rc = add_waiting(ctx);
         if (rc != CORR_OK) return rc;
         if (g.taken > 0)
             return set_err(ctx, CORR_E_STATE, "group %d holds pushes of a corr_push_steps call that failed: repeat it",

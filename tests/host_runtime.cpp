@@ -149,7 +149,7 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int)
     return hipSuccess;
 }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t *, int) { return hipErrorInvalidDevice; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { return launched("last_error"); }
 const char *hipGetErrorString(hipError_t) { return "refused"; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
 {

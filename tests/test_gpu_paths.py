@@ -316,3 +316,43 @@ def test_small_group_beside_a_producer(corrmod, source, n, dtype):
                 kw = dict(slice_=(max(0, n - 4), n))
                 _same_readout(c.finalize(1, **kw), alone.finalize(0, **kw), f"S={s + 1}")
                 _same_readout(c.finalize(0, slice_=(0, 6)), prod.finalize(0, slice_=(0, 6)), f"S={s + 1} producer")
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_error_left_by_the_caller(corrmod, graph):
+    """A HIP call of the caller's own that failed before a push, a replay or a
+    readout: the call that reports it, made again, does what it does without
+    (pushes that wait, a fold subset behind at the readout, a window)."""
+    say(f"[caller's error] graph={graph}")
+    n, S = 98304 + 33, 270
+    groups = [corrmod.GroupDesc(33, 6, 16, 2, dtype="f64", accum="f64"),
+              corrmod.GroupDesc(n, 4, 16, 2, dtype="f32", accum="kahan"),
+              corrmod.GroupDesc(40, 4, 8, 2, dtype="cf32", accum="kahan", pair=True),
+              corrmod.GroupDesc(7, 1, 600, 2, dtype="f32", accum="f64")]
+    rows = 20
+    x = [torch.randn((rows, 33), device="cuda", dtype=torch.float64), torch.randn((rows, n), device="cuda"),
+         torch.randn((rows, 80), device="cuda", dtype=torch.complex64), torch.randn((rows, 7), device="cuda")]
+
+    def again(f, *a, **kw):
+        assert corrmod.lib().hipSetDevice(1 << 20) != 0
+        try:
+            return f(*a, **kw)
+        except corrmod.CorrError:
+            return f(*a, **kw)
+        finally:  # (a replayed graph does not look at it)
+            corrmod.lib().hipGetLastError()
+
+    with corrmod.Correlator(groups, graph=graph) as c, corrmod.Correlator(groups, graph=graph) as ref:
+        for s in range(S):
+            push = [t[s % rows] for t in x]
+            again(c.push, push) if s % 50 in (0, 6) else c.push(push)
+            ref.push(push)
+            if s == 200:
+                for _ in range(2):
+                    again(c.push_steps, [t[3:10] for t in x])
+                    ref.push_steps([t[3:10] for t in x])
+            if s in (4, 70, 241, 242, S - 1):  # 14 more pushes after the replays
+                for i, g in enumerate(groups):
+                    kw = dict(slice_=(g.n_channels - 5, g.n_channels))
+                    _same_readout(again(c.finalize, i, **kw), ref.finalize(i, **kw), f"S={s + 1} group {i}")
+            assert c.n_pushes() == ref.n_pushes()

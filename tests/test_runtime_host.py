@@ -157,3 +157,25 @@ def test_refused_pass_of_a_history(host, after):
         c.finalize(0)
         for n in (5, 7):
             _every_push_once(host, n, 300)
+
+
+def test_pending_error_is_reported_before_anything_is_issued(host):
+    """An error that the caller's own HIP calls left behind: a push and a
+    readout report it and issue nothing."""
+    groups = [host.corr.GroupDesc(5, 3, 32, 2), host.corr.GroupDesc(7, 3, 8, 2), host.corr.GroupDesc(600, 3, 16, 2)]
+    frames = _frames(70, 5, 7, 600)
+    with host.context(groups) as c:
+        for s in range(70):
+            if s in (0, 10, 64):
+                before = [host.calls(k) for k in ("keep_rows", "push_split", "stage", "multi_push")]
+                host.fail("last_error")
+                with pytest.raises(host.corr.CorrError):
+                    _push(c, frames, s)
+                host.fail("last_error")
+                with pytest.raises(host.corr.CorrError):
+                    c.finalize(0)
+                assert before == [host.calls(k) for k in ("keep_rows", "push_split", "stage", "multi_push")]
+            _push(c, frames, s)
+        c.finalize(0)
+        for n in (5, 7):
+            _every_push_once(host, n, 70)
