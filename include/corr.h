@@ -240,11 +240,7 @@ int corr_bind_input(corr_ctx *ctx, int32_t group, void *dev_ptr, size_t bytes);
  * context's stream; they must stay valid until that work has run.  In graph
  * mode, a push whose pointers are all NULL (or equal to the input buffers)
  * replays the captured graph; any other pointer launches the same kernels
- * directly.  The work of a push may be issued later than the push: the forms
- * described below corr_kernel_time stage or keep the samples (in stream order)
- * and add several pushes together, at the latest in a readout; corr_sync
- * issues what waits and waits for it.  A push that fails is not counted
- * (corr_query) and may be given again.
+ * directly.
  */
 int corr_push(corr_ctx *ctx, const void *const *samples);
 
@@ -342,8 +338,7 @@ int corr_finalize_noalloc(corr_ctx *ctx, int32_t group, const corr_readout_opts 
                           int32_t *n_out, double *t, double *c, int64_t *count, double *gk_running,
                           double *gk_at_cut, double *c_per_channel);
 
-/* Wait for all work of the pushes given so far (those that wait for a
- * multi-step pass, see the notes on the forms below, are added first). */
+/* Wait for all work issued by the context. */
 int corr_sync(corr_ctx *ctx);
 
 /* Free every device allocation of the context (synchronises first). */

@@ -1901,11 +1901,6 @@ int corr_sync(corr_ctx *ctx)
 {
     if (!ctx) return CORR_E_INVALID;
     DeviceGuard dg(ctx->device);
-    if (ctx->waiting > 0) { // the work of these pushes has not been issued yet
-        int rc = pending_error(ctx);
-        if (rc == CORR_OK) rc = add_waiting(ctx);
-        if (rc != CORR_OK) return rc;
-    }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return CORR_OK;
 }

@@ -179,24 +179,3 @@ def test_pending_error_is_reported_before_anything_is_issued(host):
         c.finalize(0)
         for n in (5, 7):
             _every_push_once(host, n, 70)
-
-
-def test_sync_adds_the_waiting_pushes(host):
-    """corr_sync waits for all work of the pushes given so far: those that wait
-    for a pass are added, and a pass that is refused is reported."""
-    g = host.corr.GroupDesc(6, 3, 32, 2)
-    frames = _frames(70, 6)
-    with host.context([g]) as c:
-        c.sync()
-        for s in range(70):
-            _push(c, frames, s)
-            if s in (2, 66):
-                host.fail("multi_push")
-                with pytest.raises(host.corr.CorrError):
-                    c.sync()
-            if s in (2, 20, 66):
-                c.sync()
-                c.sync()
-                _every_push_once(host, 6, s + 1)
-        c.finalize(0)
-        _every_push_once(host, 6, 70)
