@@ -661,6 +661,39 @@ int launch_set(corr_ctx *c, const PushArgs &base, StepRef step, const std::vecto
     return CORR_OK;
 }
 
+// A single push is added by the group's per-step kernel where that is faster
+// than a pass over one row: at kSingleMin channels (pairs: kSingleMinPairs) and
+// more, of kinds whose sums of a lag take at most 8 bytes.  Both bring in the
+// same rows; the pass has twice the loads in flight to wait for at each level.
+// One push, pass / per-step: 400000 pairs of float at p = 32 88 / 68 us, of double
+// at p = 16 65 / 45, 65536 pairs 14.0 / 14.5 and 10.5 / 10.0; double, p = 16, not
+// paired, 400000 channels 48 / 42 us, 100000 12.9 / 13.9 (captured 20.1 / 18.4),
+// 32768 5.8 / 11.0.  With 16 bytes a lag the pass is never more than 7% behind and
+// up to 15% ahead (200000 complex, double sums, p = 16: 34 / 39); two pushes
+// are always faster in one pass (99999 pairs, p = 32: 30 / 38).
+constexpr int64_t kSingleMin = 98304, kSingleMinPairs = 65536;
+
+bool single_by_step(const Group &g)
+{
+    return g.n_ch >= (g.pair ? kSingleMinPairs : kSingleMin) && g.np * g.a_bytes <= 8;
+}
+
+// n pushes (1 .. kMultiT) of group i, those after `step`, push r of them at
+// rows + r pitch.
+int add_rows(corr_ctx *c, int i, StepRef step, const char *rows, int64_t pitch, int32_t n, hipStream_t st)
+{
+    if (n > 1 || !single_by_step(c->groups[(size_t)i])) {
+        HIP_TRY(c, launch_multi_push(c->pargs.g[i], step, rows, pitch, n, st));
+        return CORR_OK;
+    }
+    PushArgs pa{};
+    pa.g[0] = c->pargs.g[i];
+    pa.n_groups = 1;
+    std::vector<const void *> resolved(c->groups.size());
+    resolved[(size_t)i] = rows;
+    return launch_set(c, pa, step, std::vector<int>{i}, resolved, st);
+}
+
 // Multi-step pass of every group over its next n pushes, those after the first
 // `before`: push r of them at rows(i) + r pitch(i).  On the context's stream.
 // Where the pass of a group is refused, the groups before it remember that
@@ -671,8 +704,9 @@ int add_pushes(corr_ctx *c, int64_t before, int32_t n, Rows &&rows, Pitch &&pitc
     for (int i : c->multi_set) {
         Group &g = c->groups[(size_t)i];
         if (g.taken >= n) continue;
-        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{nullptr, before + g.taken}, rows(i) + g.taken * pitch(i),
-                                     pitch(i), n - g.taken, c->stream));
+        const int rc = add_rows(c, i, StepRef{nullptr, before + g.taken}, rows(i) + g.taken * pitch(i), pitch(i),
+                                n - g.taken, c->stream);
+        if (rc != CORR_OK) return rc;
         g.taken = n;
     }
     for (int i : c->multi_set) c->groups[(size_t)i].taken -= n;
@@ -934,9 +968,9 @@ int end_run(corr_ctx *c, const void *const *samples, const std::vector<int64_t> 
     for (int i : c->multi_set) {
         const Group &g = c->groups[(size_t)i];
         const char *hist = static_cast<const char *>(samples[i]) + (int64_t)r0 * stride[(size_t)i];
-        HIP_TRY(c, launch_multi_push(c->pargs.g[i], StepRef{c->d_step_side, each ? -(int64_t)n : 0},
-                                     g.produced() ? g.rows : hist, g.produced() ? g.row_bytes : stride[(size_t)i],
-                                     n, ust));
+        const int rc = add_rows(c, i, StepRef{c->d_step_side, each ? -(int64_t)n : 0}, g.produced() ? g.rows : hist,
+                                g.produced() ? g.row_bytes : stride[(size_t)i], n, ust);
+        if (rc != CORR_OK) return rc;
     }
     if (each) return CORR_OK;
     PushEndArgs pe{};

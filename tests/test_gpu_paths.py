@@ -356,3 +356,28 @@ def test_error_left_by_the_caller(corrmod, graph):
                     kw = dict(slice_=(g.n_channels - 5, g.n_channels))
                     _same_readout(again(c.finalize, i, **kw), ref.finalize(i, **kw), f"S={s + 1} group {i}")
             assert c.n_pushes() == ref.n_pushes()
+
+
+@pytest.mark.parametrize("dtype,accum,p,pair", [("f64", "f64", 16, False), ("f32", "kahan", 32, False),
+                                                ("f32", "kahan", 24, True), ("cf32", "f32", 16, True)])
+@pytest.mark.parametrize("graph", [False, True])
+def test_single_pushes_of_large_groups(corrmod, dtype, accum, p, pair, graph):
+    """Multi-step passes and per-step pushes of the same group in turn (one push
+    to add takes the per-step kernel at these sizes): readouts after every kind
+    of stretch, the same bits as one push at a time."""
+    n = 65536 + 3 if pair else 98304 + 3
+    say(f"[single pushes] {dtype}/{accum} p={p} pair={pair} graph={graph}")
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    real = torch.float64 if dtype == "f64" else torch.float32
+    x = torch.randn((66, (2 if pair else 1) * n * (2 if dtype == "cf32" else 1)), generator=gen, device="cuda", dtype=real)
+    g = corrmod.GroupDesc(n, 5, p, 2, dtype=dtype, accum=accum, pair=pair)
+    with corrmod.Correlator([g], graph=graph) as c, corrmod.Correlator([g], per_group=True) as ref:
+        for k in (1, 2, 1, 1, 65, 1, 3, 64, 1, 1):
+            c.push_steps([x[:k]])
+            if not graph:  # one kept push as well
+                c.push([x[65]])
+            for r in list(range(k)) + ([] if graph else [65]):
+                ref.push([x[r]])
+            if k != 2:
+                kw = dict(slice_=(n - 40, n))
+                _same_readout(c.finalize(0, **kw), ref.finalize(0, **kw), f"after {k} pushes")

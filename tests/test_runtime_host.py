@@ -179,3 +179,33 @@ def test_pending_error_is_reported_before_anything_is_issued(host):
         c.finalize(0)
         for n in (5, 7):
             _every_push_once(host, n, 70)
+
+
+@pytest.mark.parametrize("n,pair,kw,single", [
+    (98303, False, dict(points=32), "multi_push"), (98304, False, dict(points=32), "push_batched"),
+    (65535, True, dict(points=16), "multi_push"), (65536, True, dict(points=16), "push_group"),
+    (98304, False, dict(points=24, dtype="cf32", accum="kahan"), "multi_push")])
+def test_single_push_of_a_large_group(host, n, pair, kw, single):
+    """One push to add is added by the per-step kernel of a large group with
+    narrow sums, else (and with another beside it) by a multi-step pass; from
+    its row at a readout, and straight from a history."""
+    g = host.corr.GroupDesc(n, 3, m=2, pair=pair, **kw)
+    x = np.zeros((5, (2 if pair else 1) * n * (2 if "dtype" in kw else 1)), np.float32)
+    x[:, 0] = [1, 2, 3, 4, 5]
+    strides = (ctypes.c_int64 * 1)(x.strides[0])
+    with host.context([g]) as c:
+        _push(c, [x], 0)
+        c.finalize(0)
+        assert host.calls(single) == 1
+        assert host.L.corr_push_steps(c._h, 1, (ctypes.c_void_p * 1)(x[1:].ctypes.data), strides) == 0
+        assert host.calls(single) == 2 and (single == "multi_push" or host.calls("multi_push") == 0)
+        _push(c, [x], 2)
+        _push(c, [x], 3)
+        c.finalize(0)
+        assert host.calls("multi_push") == (3 if single == "multi_push" else 1)
+        _push(c, [x], 4)
+        host.fail(single)
+        with pytest.raises(host.corr.CorrError):
+            c.finalize(0)
+        c.finalize(0)
+        _every_push_once(host, n, 5)
