@@ -713,12 +713,12 @@ int add_pushes(corr_ctx *c, int64_t before, int32_t n, Rows &&rows, Pitch &&pitc
     return CORR_OK;
 }
 
-// Add the pushes that wait (the last ones counted).
-int add_waiting(corr_ctx *c)
+// Add the pushes that wait, the last of n_done.
+int add_waiting(corr_ctx *c, int64_t n_done)
 {
     if (c->waiting == 0) return CORR_OK;
     const int rc = add_pushes(
-        c, c->n_push - c->waiting, c->waiting, [&](int i) -> const char * { return c->groups[(size_t)i].rows; },
+        c, n_done - c->waiting, c->waiting, [&](int i) -> const char * { return c->groups[(size_t)i].rows; },
         [&](int i) { return c->groups[(size_t)i].row_bytes; });
     if (rc == CORR_OK) c->waiting = 0;
     return rc;
@@ -760,7 +760,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
         if (rc != CORR_OK) return rc;
     }
     if (c->waiting == kMultiT) { // no row is free: add the waiting pushes, or refuse this one
-        int rc = add_waiting(c);
+        int rc = add_waiting(c, c->n_push);
         if (rc != CORR_OK) return rc;
     }
     std::vector<const void *> resolved(ng);
@@ -912,7 +912,8 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     if (fork_updates) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (timed) HIP_TRY(c, hipEventRecord(e1, st));
     if (fork && !chained) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));
-    if (!c->counted && !c->multi_set.empty()) c->waiting += 1; // (nothing below can fail then)
+    // (this push is complete whether its pass is refused or not: the next call tries again)
+    if (!c->counted && !c->multi_set.empty() && ++c->waiting == kMultiT) (void)add_waiting(c, c->n_push + 1);
     if (!c->counted || !ends) return CORR_OK;
     PushEndArgs pe{};
     pe.step = c->d_step;
@@ -1720,7 +1721,7 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
     const bool each_push = ctx->counted || !ctx->side_set.empty() || !ctx->upd.main.empty();
     auto other_pushes = [&](int32_t r0, int32_t n) -> int {
         if (!each_push) {
-            int rc = add_waiting(ctx);
+            int rc = add_waiting(ctx, ctx->n_push);
             for (int32_t k = 0; rc == CORR_OK && k < n; k += kMultiT) {
                 const int32_t m = std::min(kMultiT, n - k);
                 rc = add_pushes(
@@ -1998,7 +1999,7 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
 
     {
         int rc = pending_error(ctx);
-        if (rc == CORR_OK) rc = add_waiting(ctx);
+        if (rc == CORR_OK) rc = add_waiting(ctx, ctx->n_push);
         if (rc != CORR_OK) return rc;
         if (g.taken > 0)
             return set_err(ctx, CORR_E_STATE, "group %d holds pushes of a corr_push_steps call that failed: repeat it",

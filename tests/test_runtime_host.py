@@ -73,7 +73,7 @@ def _every_push_once(host, n_ch, steps):
 @pytest.mark.parametrize("retry", ["push", "finalize"])
 def test_refused_pass_of_waiting_pushes(host, after, retry):
     """A pass that the runtime refuses, for the first or the second of two
-    groups, after 64 pushes or at a readout: the call that needed it fails, no
+    groups, after 64 pushes or at a readout: a readout that needed it fails, no
     push is written past the rows, and after the next calls every push is in
     the sums of both groups once."""
     groups = [host.corr.GroupDesc(n, 3, 32, 2) for n in (5, 7)]
@@ -97,10 +97,9 @@ def test_refused_pass_of_waiting_pushes(host, after, retry):
                 s += 1
             except host.corr.CorrError:
                 refused += 1
-                assert refused == 1
             assert c.n_pushes() == s
         c.finalize(0)
-        assert refused == 1 and host.L.stub_out_of_range() == 0
+        assert refused == (retry == "finalize") and host.L.stub_out_of_range() == 0
         for n in (5, 7):
             _every_push_once(host, n, steps)
 
