@@ -288,6 +288,8 @@ AB = {("f32", "f64"): 8, ("f32", "kahan"): 8, ("f32", "f32"): 4, ("f64", "f64"):
 
 
 DEFER_T = 256   # pushes per block of the block-deferred form (the library's default T)
+# channels of a fold subset at least (kFoldMinChannels of csrc/corr_internal.h)
+FOLD_MIN_CHANNELS = 98304
 WINDOW_T = 64   # pushes per block of the block-deferred window
 
 
@@ -341,8 +343,8 @@ def group_channels(g, tw, j):
     """Channels of tile group j (at most T groups of contiguous tiles) of a block-deferred
     group."""
     n_tiles = -(-g["n"] // tw)
-    # at most one tile group per push of a block, of at least 98304 channels
-    tpg = max(-(-n_tiles // block_of(g)), min(n_tiles, -(-98304 // tw)))
+    # at most one tile group per push of a block, of at least FOLD_MIN_CHANNELS
+    tpg = max(-(-n_tiles // block_of(g)), min(n_tiles, -(-FOLD_MIN_CHANNELS // tw)))
     t0, t1 = j * tpg, min((j + 1) * tpg, n_tiles)
     if t0 >= t1:
         return 0
@@ -783,6 +785,14 @@ def run(args):
                    "push_calls": ("one captured HIP graph per chunk of %d pushes (corr_push_steps "
                                   "with CORR_FLAG_GRAPH)" % chunk if use_graph
                                   else "one corr_push per step"),
+                   # (CORR_FLAG_TIMING: the stamps and events take every push by itself)
+                   "per_step_groups": ("multi-step passes of up to 64 pushes inside a captured "
+                                       "chunk where a group has them, one end kernel per push"
+                                       if use_graph else
+                                       "one update and one end kernel per push" +
+                                       ("" if args.direct or mode == "per_group" else
+                                        " (untimed contexts: passes of up to 64 pushes where a "
+                                        "group has them, no end kernel)")),
                    "fold_block": {str(i): g["T"] for i, g in enumerate(wl["groups"]) if "T" in g},
                    "producer_stream": {0: "the context's stream, before the other updates",
                                        1: ("a side stream with the per-step updates, forked and "
@@ -924,8 +934,11 @@ def mode_leg(args, wl, descs, gens, bufs, tuned, mode, chunk, graph, headline_va
 
     from paper_2503_07526_amd import Correlator
     n_total = sum(g["n"] for g in wl["groups"])
-    corr = Correlator(descs, per_group=(mode == "per_group"), tuning=tuned, graph=graph,
+    # (timed like the headline's context: without the flag a push takes other
+    # kernels, and the ratio would not be that of the issue forms alone)
+    corr = Correlator(descs, per_group=(mode == "per_group"), tuning=tuned, graph=graph, timing=True,
                       direct=args.direct, rhok_valu=args.rhok_valu)
+    corr.set_timing_stride(args.timing_stride)
     T0 = max([block_of(g) for g in wl["groups"] if deferred(g, args.direct)], default=0)
 
     def chunk_run(n):
