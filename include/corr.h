@@ -77,7 +77,8 @@ enum corr_source {
                              channels 3q+1 and 3q+2.  Components of n must
                              lie within +-15; n = 0 is rejected.  Any finite
                              velocities: each component is scaled by a
-                             power of two per block of about 1000 atoms
+                             power of two per block of atoms (n_atoms over
+                             the blocks that fill the chip, but at least 128)
                              before the fp16 split (see CORR_FLAG_RHOK_VALU),
                              so products keep about 22 bits relative to
                              the largest |v_alpha| of the block; J(k) must
@@ -241,6 +242,11 @@ int corr_bind_input(corr_ctx *ctx, int32_t group, void *dev_ptr, size_t bytes);
  * mode, a push whose pointers are all NULL (or equal to the input buffers)
  * replays the captured graph; any other pointer launches the same kernels
  * directly.
+ * The samples are read by the work of this call, but their products may be
+ * added later: by the fold of a later push in the block-deferred forms, and 64
+ * pushes at a time where a group takes multi-step passes (both described below
+ * corr_kernel_time), at the latest by a readout.
+ * A push that fails is not counted (corr_query) and may be given again.
  */
 int corr_push(corr_ctx *ctx, const void *const *samples);
 
@@ -338,7 +344,9 @@ int corr_finalize_noalloc(corr_ctx *ctx, int32_t group, const corr_readout_opts 
                           int32_t *n_out, double *t, double *c, int64_t *count, double *gk_running,
                           double *gk_at_cut, double *c_per_channel);
 
-/* Wait for all work issued by the context. */
+/* Wait for all work issued by the context: after it the samples of every push
+ * so far may be overwritten.  Pushes that wait for a fold or for a multi-step
+ * pass (see corr_push) are not added by it; a readout adds them. */
 int corr_sync(corr_ctx *ctx);
 
 /* Free every device allocation of the context (synchronises first). */
@@ -349,7 +357,9 @@ int corr_destroy(corr_ctx *ctx);
 const char *corr_last_error(const corr_ctx *ctx);
 
 /* Device bytes of correlator state held by a group (ring and accumulator
- * planes, padded to whole tiles). */
+ * planes, padded to whole tiles).  Not counted: the group's input buffer, the
+ * rows in which pushes wait for a multi-step pass (64 times a push's bytes)
+ * and the producers' partial sums. */
 int corr_state_bytes(const corr_ctx *ctx, int32_t group, int64_t *bytes);
 
 /* With CORR_FLAG_TIMING: synchronise and return summed device times from HIP
@@ -432,7 +442,11 @@ int corr_get_tuning(const corr_ctx *ctx, corr_tuning *out);
  * shape, choose overlap_producers on trial contexts whose sample-fed groups
  * and producer atom counts are scaled by one factor so that the largest group
  * has at most 2^25 channels (the concurrent kernels keep their balance), and
- * return the result in *out.  The choice is cached in a text file of JSON lines (cache_path, or
+ * return the result in *out.  The trials push step by step with corr_push (with
+ * CORR_FLAG_GRAPH: one captured push, replayed); a run of pushes captured by
+ * corr_push_steps takes multi-step passes and one end kernel instead, so for
+ * programs that push in such runs the issue order is ranked by a neighbouring
+ * program.  The choice is cached in a text file of JSON lines (cache_path, or
  * NULL for $CORR_TUNE_CACHE, else $HOME/.cache/corr_gfx950_tune.jsonl, else
  * no cache) keyed by the device architecture, the flags and the group
  * descriptors; a cached entry is returned without timing unless force != 0.

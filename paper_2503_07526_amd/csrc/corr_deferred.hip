@@ -14,13 +14,16 @@
 // after a flush is that of Algorithm 1 after the same pushes, up to the
 // grouping of the floating-point sums.
 //
-// Staggering: the tiles are split into kFlushGroups groups and group j folds
-// block q (pushes T(q-1)+1 .. Tq) at push Tq + j, so every push flushes about
-// 1/kFlushGroups of the channels and the per-push cost is flat.  The level-0
-// ring therefore holds P0 = 2T + p slots: the block being folded, up to T - 1
-// pushes staged after it, and the p values before the block that its lags
-// reach back to.  Each group's last folded block is kept in a device array
-// (and mirrored on the host) so that a flush is never applied twice.
+// Staggering: the tiles are split into at most T groups of at least
+// kFoldMinChannels channels, and group j folds block q (pushes T(q-1)+1 .. Tq)
+// at push Tq + j.  From T kFoldMinChannels channels on every push flushes 1/T of
+// them, at a flat cost; a smaller set of channels has fewer groups and folds
+// on the first pushes of a block only.  The level-0 ring therefore holds
+// P0 = 2T + p slots: the block being folded, up to T - 1 pushes staged after
+// it, and the p values before the block that its lags reach back to.  The host
+// records each group's last folded block and asks for no fold twice; contexts
+// whose captured pushes replay at any count also keep the record in a device
+// array, which the fold kernel looks at.
 //
 // State is touched once per flush and not again for T pushes, so the flush
 // streams it with non-temporal loads and stores.

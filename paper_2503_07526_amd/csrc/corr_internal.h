@@ -222,7 +222,7 @@ struct KeepRow {
 };
 // A small group's copy may ride on a producer's final kernel (an extra block)
 // instead of a launch of its own: 32 pushes of the momentum densities of 5e6
-// atoms beside a 3-channel group, and a readout, 704 us instead of 755.
+// atoms beside a 3-channel group, and a readout, 702 us instead of 763.
 constexpr int64_t kRiderBytes = 16 << 10;
 
 struct KeepArgs {

@@ -304,6 +304,12 @@ __global__ __launch_bounds__(256) void keep_rows_kernel(KeepArgs a)
 
 } // namespace
 
+// m = 2 is built in (a level's values are means of two), and a kernel is built
+// for each point count, so that a thread's share of the lags (P / 8) is held in
+// registers: 16 and 32, which the library's workloads use, and 24 between them
+// (15 kernels a count).  64 pushes of 150000 float pairs, pass / push by push: p =
+// 16 118 / 1044 us, 24 165 / 1451, 32 184 / 1852.  Other counts, for which nothing
+// has been measured, keep the per-step push.
 bool multi_supported(int kind, int p, int m, bool pair)
 {
     return m == 2 && (p == 16 || p == 24 || p == 32) && !(pair && kind == K_CF64_F64);

@@ -464,17 +464,19 @@ DeferredArgs deferred_args(const corr_ctx *c, int i)
     return da;
 }
 
-// Scheduled flush of every block-deferred group for the push being issued
-// (tile group S mod kDeferT folds block S / kDeferT if not done yet); with
-// events, f0/f1 bracket the fold kernels.  The flush is recorded as done by
-// the push's last kernel (push_end).
+// Scheduled flush of every block-deferred group for the push S being issued
+// (tile group S mod T folds block S / T if not done yet); with events, f0/f1
+// bracket the fold kernels.  The host records the flush after the push
+// (mirror_flushes); contexts with device counters also on the device, in the
+// end kernel of the push or of its captured run.
 int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1, const Run *run)
 {
     if (f0) HIP_TRY(c, hipEventRecord(f0, st));
     for (int i : c->deferred_set) {
         // no launch for a tile group without tiles or whose block is folded
-        // already, or before the first block is complete (a captured push keeps its launch, which then exits at
-        // once: it replays at any push count; timed pushes keep theirs too)
+        // already, or before the first block is complete (a captured push
+        // keeps its launch, which then exits at once: it replays at any push
+        // count; timed pushes keep theirs too)
         const Group &g = c->groups[(size_t)i];
         const int64_t S = c->n_push + 1;
         if (st == c->stream && !c->d_stamps &&
@@ -726,9 +728,12 @@ int add_waiting(corr_ctx *c, int64_t n_done)
 
 // Issue one push of every group on stream `st` with the given per-group
 // sample pointers (already resolved, never NULL).  Order on the main stream:
-// staging of block-deferred groups, the producers, the per-step push of the
-// other groups, the flush of the block-deferred groups, the push end (flush
-// records and step counter).  overlap_producers = 1 forks the producers onto
+// the copies to waiting rows, staging of block-deferred groups, the producers
+// (a small copy or staging may ride on the first one's final kernel), the
+// per-step push of the groups without waiting rows, the flush of the
+// block-deferred groups, the multi-step pass when this push fills the rows;
+// with device counters an end kernel (flush records and step counter), for
+// this push or for the captured run that it is part of.  overlap_producers = 1 forks the producers onto
 // the side stream at the start of the push (before the staging), followed
 // there by the per-step push of every direct group
 // when block-deferred groups keep the main stream busy with their flush, else
@@ -2109,71 +2114,71 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
         }
         if (want_slice && pin_slice) std::memcpy(c_per_channel, ctx->pinned + s_bytes, slice_bytes);
     } else {
-    // scratch: partial (ne * bpe * 2 doubles) and, where the pinned buffer does not hold them,
-    // sums (ne * 2 doubles) and slice (n_slice * ne doubles or pairs)
-    const size_t part_bytes = (size_t)ne * bpe * 2 * sizeof(double);
-    const size_t sum_bytes = (size_t)ne * 2 * sizeof(double);
-    const size_t slice_bytes = (size_t)n_slice * ne * (cplx ? 2 : 1) * sizeof(double);
-    // The sums, and a slice that fits behind them, are written to the pinned
-    // buffer by the kernels themselves.
-    const bool pin_sums = sum_bytes <= kPinnedBytes;
-    const bool pin_slice = pin_sums && sum_bytes + slice_bytes <= kPinnedBytes;
-    char *sc = nullptr;
-    {
-        int rc = readout_scratch(ctx, noalloc, part_bytes + (pin_sums ? 0 : sum_bytes) + (pin_slice ? 0 : slice_bytes), &sc);
-        if (rc != CORR_OK) return rc;
-    }
-    double *d_part = reinterpret_cast<double *>(sc);
-    double *d_sum = reinterpret_cast<double *>(pin_sums ? ctx->pinned : sc + part_bytes);
-    double *d_slice = reinterpret_cast<double *>(pin_slice ? ctx->pinned + sum_bytes
-                                                           : sc + part_bytes + (pin_sums ? 0 : sum_bytes));
-    ReduceArgs ra{};
-    ra.state = g.state;
-    ra.tile_bytes = g.tile_bytes;
-    ra.tw = tw;
-    ra.kind = g.kind;
-    for (int i = 0; i < ne; ++i) {
-        const Entry &e = ent[(size_t)i];
-        if (e.level + 1 == ra.n_levels) continue;
-        ra.level_e[e.level] = i; // its first entry
-        ra.level_n[e.level] = e.count + e.lag;
-        ra.n_levels = e.level + 1;
-    }
-    ra.lag0 = g.lag0;
-    ra.lvl0_bytes = g.lvl0_bytes;
-    ra.lvlk_bytes = g.lvlk_bytes;
-    ra.acc0 = (int64_t)(g.pair ? 2 : 1) * g.p0 * rowS;
-    ra.acck = (int64_t)(g.pair ? 2 : 1) * g.p * rowS;
-    ra.lo0 = (int64_t)g.p * rowA;
-    ra.lok = (int64_t)g.nlk * rowA;
-    ra.row_bytes = rowA;
-    ra.n_entries = ne;
-    ra.blocks_per_entry = bpe;
-    ra.ch_begin = cb;
-    ra.ch_end = ce;
-    ra.partial = d_part;
-    ra.out = d_sum;
-    ra.wlpb = g.wdef ? window_lags_per_block(g.p) : 0;
-    ra.p0 = g.p0;
-    ra.n_push = S;
-    HIP_TRY(ctx, launch_reduce(ra, ctx->stream));
-    if (!pin_sums)
-        HIP_TRY(ctx, hipMemcpyAsync(sums.data(), d_sum, sum_bytes, hipMemcpyDeviceToHost, ctx->stream));
-    if (want_slice) {
-        ReduceArgs rs = ra;
-        rs.ch_begin = sb;
-        rs.ch_end = se;
-        rs.out = d_slice;
-        rs.norm = norm;
-        rs.cplx = cplx ? 1 : 0;
-        HIP_TRY(ctx, launch_gather(rs, ctx->stream));
-        if (!pin_slice)
-            HIP_TRY(ctx, hipMemcpyAsync(c_per_channel, d_slice, slice_bytes, hipMemcpyDeviceToHost,
-                                        ctx->stream));
-    }
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    if (pin_sums) std::memcpy(sums.data(), ctx->pinned, sum_bytes);
-    if (want_slice && pin_slice) std::memcpy(c_per_channel, ctx->pinned + sum_bytes, slice_bytes);
+        // scratch: partial (ne * bpe * 2 doubles) and, where the pinned buffer does not hold them,
+        // sums (ne * 2 doubles) and slice (n_slice * ne doubles or pairs)
+        const size_t part_bytes = (size_t)ne * bpe * 2 * sizeof(double);
+        const size_t sum_bytes = (size_t)ne * 2 * sizeof(double);
+        const size_t slice_bytes = (size_t)n_slice * ne * (cplx ? 2 : 1) * sizeof(double);
+        // The sums, and a slice that fits behind them, are written to the pinned
+        // buffer by the kernels themselves.
+        const bool pin_sums = sum_bytes <= kPinnedBytes;
+        const bool pin_slice = pin_sums && sum_bytes + slice_bytes <= kPinnedBytes;
+        char *sc = nullptr;
+        {
+            int rc = readout_scratch(ctx, noalloc, part_bytes + (pin_sums ? 0 : sum_bytes) + (pin_slice ? 0 : slice_bytes), &sc);
+            if (rc != CORR_OK) return rc;
+        }
+        double *d_part = reinterpret_cast<double *>(sc);
+        double *d_sum = reinterpret_cast<double *>(pin_sums ? ctx->pinned : sc + part_bytes);
+        double *d_slice = reinterpret_cast<double *>(pin_slice ? ctx->pinned + sum_bytes
+                                                               : sc + part_bytes + (pin_sums ? 0 : sum_bytes));
+        ReduceArgs ra{};
+        ra.state = g.state;
+        ra.tile_bytes = g.tile_bytes;
+        ra.tw = tw;
+        ra.kind = g.kind;
+        for (int i = 0; i < ne; ++i) {
+            const Entry &e = ent[(size_t)i];
+            if (e.level + 1 == ra.n_levels) continue;
+            ra.level_e[e.level] = i; // its first entry
+            ra.level_n[e.level] = e.count + e.lag;
+            ra.n_levels = e.level + 1;
+        }
+        ra.lag0 = g.lag0;
+        ra.lvl0_bytes = g.lvl0_bytes;
+        ra.lvlk_bytes = g.lvlk_bytes;
+        ra.acc0 = (int64_t)(g.pair ? 2 : 1) * g.p0 * rowS;
+        ra.acck = (int64_t)(g.pair ? 2 : 1) * g.p * rowS;
+        ra.lo0 = (int64_t)g.p * rowA;
+        ra.lok = (int64_t)g.nlk * rowA;
+        ra.row_bytes = rowA;
+        ra.n_entries = ne;
+        ra.blocks_per_entry = bpe;
+        ra.ch_begin = cb;
+        ra.ch_end = ce;
+        ra.partial = d_part;
+        ra.out = d_sum;
+        ra.wlpb = g.wdef ? window_lags_per_block(g.p) : 0;
+        ra.p0 = g.p0;
+        ra.n_push = S;
+        HIP_TRY(ctx, launch_reduce(ra, ctx->stream));
+        if (!pin_sums)
+            HIP_TRY(ctx, hipMemcpyAsync(sums.data(), d_sum, sum_bytes, hipMemcpyDeviceToHost, ctx->stream));
+        if (want_slice) {
+            ReduceArgs rs = ra;
+            rs.ch_begin = sb;
+            rs.ch_end = se;
+            rs.out = d_slice;
+            rs.norm = norm;
+            rs.cplx = cplx ? 1 : 0;
+            HIP_TRY(ctx, launch_gather(rs, ctx->stream));
+            if (!pin_slice)
+                HIP_TRY(ctx, hipMemcpyAsync(c_per_channel, d_slice, slice_bytes, hipMemcpyDeviceToHost,
+                                            ctx->stream));
+        }
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        if (pin_sums) std::memcpy(sums.data(), ctx->pinned, sum_bytes);
+        if (want_slice && pin_slice) std::memcpy(c_per_channel, ctx->pinned + sum_bytes, slice_bytes);
     }
 
     const double tunit = (double)g.d.update_every * g.d.dt;
