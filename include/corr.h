@@ -403,7 +403,8 @@ int corr_state_bytes(const corr_ctx *ctx, int32_t group, int64_t *bytes);
  * with the operations of single pushes in their order: the same results bit
  * for bit.  A readout adds the waiting pushes first.  Not with
  * CORR_FLAG_DIRECT or CORR_FLAG_PER_GROUP; with CORR_FLAG_GRAPH inside
- * corr_push_steps only; not with CORR_FLAG_TIMING alone.
+ * corr_push_steps only (rows for the samples of producers only: sample groups
+ * are added from the histories); not with CORR_FLAG_TIMING alone.
  *
  * Block-deferred window: a group with one level (b = 1), p >= 512 points and
  * single-precision samples (real or complex, any accumulator; not pair

@@ -75,7 +75,8 @@ struct Group {
     int p0 = 0;            // ring rows of level 0
     bool pair = false;     // channels correlate (x, y) pairs
     // per-step group whose pushes wait in rows [kMultiT] of row_bytes each
-    // until a multi-step pass adds them (corr_ctx::waiting of them)
+    // until a multi-step pass adds them (corr_ctx::waiting of them); in graph
+    // contexts only a producer's samples have rows
     bool multi = false;
     char *rows = nullptr;
     int64_t row_bytes = 0;
@@ -1458,6 +1459,11 @@ int corr_create(const corr_group_desc *groups, int32_t n_groups, int32_t device,
             Group &g = c->groups[(size_t)i];
             if (g.deferred || g.wdef || is_window(c->pargs.g[i]) || !multi_supported(g.kind, g.p, g.m, g.pair))
                 continue;
+            if (c->counted && !g.produced()) { // no push of it waits: captured runs read the history
+                g.multi = true;
+                c->multi_set.push_back(i);
+                continue;
+            }
             const int64_t row = ((int64_t)(g.pair ? 2 : 1) * g.n_ch * g.s_bytes + 255) / 256 * 256;
             if ((size_t)row * kMultiT > left) continue;
             if (hipMalloc(&g.rows, (size_t)row * kMultiT) != hipSuccess) {

@@ -82,6 +82,12 @@ void stub_reset()
 void stub_fail(const char *name, int after) { failing[name] = after; }
 int stub_calls(const char *name) { return calls[name]; }
 int stub_out_of_range() { return out_of_range; }
+int64_t stub_allocated()
+{
+    int64_t n = 0;
+    for (const auto &a : allocations) n += (int64_t)a.second;
+    return n;
+}
 int stub_added(int64_t n_ch, int64_t *push, float *value, int cap)
 {
     const auto &v = added[n_ch];

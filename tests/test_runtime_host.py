@@ -208,3 +208,20 @@ def test_single_push_of_a_large_group(host, n, pair, kw, single):
             c.finalize(0)
         c.finalize(0)
         _every_push_once(host, n, 5)
+
+
+def test_waiting_rows_only_where_pushes_wait(host):
+    """Device memory of a group with multi-step passes: 64 rows of its pushes'
+    samples where they wait there, none in a context with captured pushes (a
+    captured run adds sample groups straight from the history)."""
+    n, row = 5000, 5000 * 4 // 256 * 256 + 256
+    host.L.stub_allocated.restype = ctypes.c_int64
+
+    def bytes_of(**kw):
+        before = host.L.stub_allocated()
+        with host.context([host.corr.GroupDesc(n, 3, 32, 2)], **kw):
+            return host.L.stub_allocated() - before
+
+    plain = bytes_of(direct=True)
+    assert bytes_of() - plain == 64 * row
+    assert bytes_of(graph=True) == plain
