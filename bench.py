@@ -613,8 +613,8 @@ def run(args):
         tuning = dict(tuning or {}, overlap_producers=args.overlap)
     # Block-deferred workloads are timed as captured HIP graphs (one graph per
     # chunk of pushes, corr_push_steps on a CORR_FLAG_GRAPH context), the eager
-    # form beside them (1.5 to 6% slower on every such line once the timing
-    # stamps sample one push in timing_stride); the others eagerly, one
+    # form beside them (0.216-0.220 ms a push against 0.170 on the default line,
+    # both with the stamps of one push in timing_stride); the others eagerly, one
     # corr_push per step.
     use_graph = (not args.eager and not args.replay and not args.direct and mode != "per_group"
                  and any(deferred(g) for g in wl["groups"]))
