@@ -173,6 +173,7 @@ struct corr_ctx {
     };
     std::vector<StepsGraph> steps_graphs;
     std::vector<int> deferred_set; // context group indices in the block-deferred form
+    bool missed = false; // a fold scheduled for pushes already counted was refused
     // kernel timing (CORR_FLAG_TIMING): pool 0 per push, pool 1 per flush
     // fold, pool 2 per k-density producer launch
     struct EventPool {
@@ -478,7 +479,7 @@ int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1, co
         // already, or before the first block is complete (a captured push
         // keeps its launch, which then exits at once: it replays at any push
         // count; timed pushes keep theirs too)
-        const Group &g = c->groups[(size_t)i];
+        Group &g = c->groups[(size_t)i];
         const int64_t S = c->n_push + 1;
         if (st == c->stream && !c->d_stamps &&
             (S < g.T || (S % g.T) * g.tiles_per_group >= g.n_tiles ||
@@ -488,6 +489,8 @@ int launch_flushes(corr_ctx *c, hipStream_t st, hipEvent_t f0, hipEvent_t f1, co
         da.step = step_main(c, run);
         da.stamps = c->d_stamps; // the catch-up flushes of a readout carry none
         HIP_TRY(c, launch_flush_fold(da, st));
+        // (at once: the push may be given again after a refused launch)
+        if (!c->counted) g.flushed[(size_t)(S % g.T)] = S / g.T;
     }
     if (f1) HIP_TRY(c, hipEventRecord(f1, st));
     return CORR_OK;
@@ -533,7 +536,7 @@ int commit_block(corr_ctx *c, const std::vector<int> &idx, int64_t q, int32_t ad
 // through them in order, so there is one run).
 int fold_range(corr_ctx *c, int i, int64_t q, int j0, int j1)
 {
-    const Group &g = c->groups[(size_t)i];
+    Group &g = c->groups[(size_t)i];
     for (int j = j0; j < j1;) {
         if (g.flushed[(size_t)j] >= q) {
             ++j;
@@ -547,6 +550,10 @@ int fold_range(corr_ctx *c, int i, int64_t q, int j0, int j1)
         da.tile_first = std::min(g.n_tiles, j * g.tiles_per_group);
         da.tile_end = std::min(g.n_tiles, e * g.tiles_per_group);
         if (da.tile_end > da.tile_first) HIP_TRY(c, launch_flush_fold(da, c->stream));
+        // (where the host's record alone decides, it holds every launch made, so
+        // that a call repeated after a refused one folds nothing again)
+        if (!c->counted)
+            for (int k = j; k < e; ++k) g.flushed[(size_t)k] = q;
         j = e;
     }
     return CORR_OK;
@@ -572,7 +579,27 @@ int catch_up_flushes(corr_ctx *c, int gi)
     const Group &g = c->groups[(size_t)gi];
     const int64_t q = c->n_push / g.T;
     for (int64_t f : g.flushed)
+        if (f > q)
+            return set_err(c, CORR_E_STATE, "group %d has folded pushes of a call that failed: repeat it", gi);
+    for (int64_t f : g.flushed)
         if (f < q) return fold_all(c, std::vector<int>{gi}, q);
+    return CORR_OK;
+}
+
+// The folds that were scheduled for pushes already counted and refused: block
+// n_push / T of the tile groups whose turn has come, the block before of the others.
+int fold_missed(corr_ctx *c)
+{
+    if (!c->missed) return CORR_OK;
+    for (int i : c->deferred_set) {
+        const int T = c->groups[(size_t)i].T;
+        const int64_t q = c->n_push / T;
+        const int next = (int)(c->n_push % T) + 1;
+        int rc = q >= 1 ? fold_range(c, i, q, 0, next) : CORR_OK;
+        if (rc == CORR_OK && q >= 2) rc = fold_range(c, i, q - 1, next, T);
+        if (rc != CORR_OK) return rc;
+    }
+    c->missed = false;
     return CORR_OK;
 }
 
@@ -763,6 +790,7 @@ int issue_push(corr_ctx *c, const void *const *src, hipStream_t st, bool with_fl
     const size_t ng = c->groups.size();
     if (st == c->stream) {
         int rc = pending_error(c);
+        if (rc == CORR_OK) rc = fold_missed(c);
         if (rc != CORR_OK) return rc;
     }
     if (c->waiting == kMultiT) { // no row is free: add the waiting pushes, or refuse this one
@@ -1772,7 +1800,10 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
             HIP_TRY(ctx, launch_stage_rows(ga, StepRef{nullptr, S}, stride[(size_t)i], n, ctx->stream));
         }
         int rc = other_pushes(r0, n);
-        if (rc != CORR_OK) return rc;
+        if (rc != CORR_OK) { // (those counted have no folds yet: the next call makes them)
+            ctx->missed = true;
+            return rc;
+        }
         // push s folds block s / T of tile group s % T
         for (int i : ctx->deferred_set) {
             Group &g = ctx->groups[(size_t)i];
@@ -1781,7 +1812,10 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
                 const int j0 = (int)(s - q * g.T), j1 = (int)(e - q * g.T);
                 if (q >= 1) {
                     rc = fold_range(ctx, i, q, j0, j1);
-                    if (rc != CORR_OK) return rc;
+                    if (rc != CORR_OK) { // (the pushes are counted: the next call folds them)
+                        ctx->missed = true;
+                        return rc;
+                    }
                     for (int j = j0; j < j1; ++j) g.flushed[(size_t)j] = std::max(g.flushed[(size_t)j], q);
                 }
                 s = e;
@@ -1791,6 +1825,7 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
     };
     {
         int rc = pending_error(ctx);
+        if (rc == CORR_OK) rc = fold_missed(ctx);
         if (rc != CORR_OK) return rc;
     }
     int32_t r = 0;
@@ -1819,14 +1854,18 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
                 int rc = fold_all(ctx, ctx->deferred_set, q);
                 if (rc != CORR_OK) return rc;
             }
-            // the other groups' pushes
-            if (others) {
+            // the other groups' pushes: after the block's folds where the host's
+            // record decides, so that nothing is counted whose fold is refused
+            if (others && ctx->counted) {
                 int rc = other_pushes(r, n);
                 if (rc != CORR_OK) return rc;
             }
             // block q + 1 of every block-deferred group, read from the history
             // (row `from` of the block is row r)
             for (int i : ctx->deferred_set) {
+                Group &g = ctx->groups[(size_t)i];
+                if (!ctx->counted && *std::min_element(g.flushed.begin(), g.flushed.end()) > q)
+                    continue; // (by a call that failed after it)
                 DeferredArgs da = deferred_args(ctx, i);
                 da.fixed_group = -2;
                 da.fixed_block = q + 1;
@@ -1837,6 +1876,11 @@ int corr_push_steps(corr_ctx *ctx, int32_t n_steps, const void *const *samples,
                 da.hist_stride = stride[(size_t)i];
                 da.stamps = ctx->d_stamps;
                 HIP_TRY(ctx, launch_history_fold(da, ctx->stream));
+                if (!ctx->counted) g.flushed.assign(g.flushed.size(), q + 1);
+            }
+            if (others && !ctx->counted) {
+                int rc = other_pushes(r, n);
+                if (rc != CORR_OK) return rc;
             }
             // (the other groups' pushes advanced the counter)
             int rc = commit_block(ctx, ctx->deferred_set, q + 1, others ? 0 : n, true);
@@ -2010,6 +2054,7 @@ int finalize_impl(corr_ctx *ctx, int32_t group, const corr_readout_opts *opts, i
 
     {
         int rc = pending_error(ctx);
+        if (rc == CORR_OK) rc = fold_missed(ctx);
         if (rc == CORR_OK) rc = add_waiting(ctx, ctx->n_push);
         if (rc != CORR_OK) return rc;
         if (g.taken > 0)

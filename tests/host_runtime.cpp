@@ -27,6 +27,7 @@ struct Added {
     float value;
 };
 std::map<int64_t, std::vector<Added>> added; // by the group's channel count
+std::map<int64_t, std::vector<int64_t>> folded; // by channel count: block * 1e6 + tile group, in order
 int out_of_range = 0;
 
 hipError_t launched(const char *name)
@@ -68,6 +69,22 @@ hipError_t push_one(const char *name, const GroupArgs &g, StepRef step)
     return e;
 }
 
+// The tile groups that a fold launch covers, and their block.
+void fold(const DeferredArgs &a)
+{
+    int64_t q = a.fixed_block, j0, j1;
+    if (a.fixed_group == -2) {
+        j0 = a.tile_first / a.tiles_per_group;
+        j1 = (a.tile_end + a.tiles_per_group - 1) / a.tiles_per_group;
+    } else {
+        const int64_t s = a.step.count + 1;
+        q = s / a.g.defer_t;
+        j0 = s % a.g.defer_t;
+        j1 = j0 + 1;
+    }
+    for (int64_t j = j0; j < j1; ++j) folded[a.g.n_ch].push_back(q * 1000000 + j);
+}
+
 } // namespace
 
 extern "C" {
@@ -77,6 +94,7 @@ void stub_reset()
     calls.clear();
     failing.clear();
     added.clear();
+    folded.clear();
     out_of_range = 0;
 }
 void stub_fail(const char *name, int after) { failing[name] = after; }
@@ -95,6 +113,13 @@ int stub_added(int64_t n_ch, int64_t *push, float *value, int cap)
         push[i] = v[(size_t)i].push;
         value[i] = v[(size_t)i].value;
     }
+    return (int)v.size();
+}
+
+int stub_folded(int64_t n_ch, int64_t *out, int cap)
+{
+    const auto &v = folded[n_ch];
+    for (int i = 0; i < (int)v.size() && i < cap; ++i) out[i] = v[(size_t)i];
     return (int)v.size();
 }
 
@@ -274,8 +299,18 @@ hipError_t launch_momentum(const MomentumArgs &, const KeepRow &rider, hipStream
 }
 hipError_t launch_stage(const GroupArgs &, StepRef, hipStream_t) { return launched("stage"); }
 hipError_t launch_stage_rows(const GroupArgs &, StepRef, int64_t, int, hipStream_t) { return launched("stage"); }
-hipError_t launch_flush_fold(const DeferredArgs &, hipStream_t) { return launched("fold"); }
-hipError_t launch_history_fold(const DeferredArgs &, hipStream_t) { return launched("fold"); }
+hipError_t launch_flush_fold(const DeferredArgs &a, hipStream_t)
+{
+    const hipError_t e = launched("fold");
+    if (e == hipSuccess) fold(a);
+    return e;
+}
+hipError_t launch_history_fold(const DeferredArgs &a, hipStream_t)
+{
+    const hipError_t e = launched("history_fold");
+    if (e == hipSuccess) fold(a);
+    return e;
+}
 hipError_t launch_push_end(const PushEndArgs &, hipStream_t) { return launched("push_end"); }
 hipError_t launch_reduce(const ReduceArgs &, hipStream_t) { return launched("reduce"); }
 hipError_t launch_gather(const ReduceArgs &, hipStream_t) { return launched("gather"); }

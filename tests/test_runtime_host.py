@@ -166,14 +166,14 @@ def test_pending_error_is_reported_before_anything_is_issued(host):
     with host.context(groups) as c:
         for s in range(70):
             if s in (0, 10, 64):
-                before = [host.calls(k) for k in ("keep_rows", "push_split", "stage", "multi_push")]
+                before = [host.calls(k) for k in ("keep_rows", "push_batched", "stage", "multi_push")]
                 host.fail("last_error")
                 with pytest.raises(host.corr.CorrError):
                     _push(c, frames, s)
                 host.fail("last_error")
                 with pytest.raises(host.corr.CorrError):
                     c.finalize(0)
-                assert before == [host.calls(k) for k in ("keep_rows", "push_split", "stage", "multi_push")]
+                assert before == [host.calls(k) for k in ("keep_rows", "push_batched", "stage", "multi_push")]
             _push(c, frames, s)
         c.finalize(0)
         for n in (5, 7):
@@ -225,3 +225,122 @@ def test_waiting_rows_only_where_pushes_wait(host):
     plain = bytes_of(direct=True)
     assert bytes_of() - plain == 64 * row
     assert bytes_of(graph=True) == plain
+
+
+@pytest.mark.parametrize("after", range(9))
+def test_refused_fold(host, after):
+    """A fold that the runtime refuses, in a push, in the rows of a short replay
+    or at a readout that folds what is behind: after the call made again (from
+    where the count stands) every subset of both groups has folded every block
+    once, in order."""
+    ns, T = (3 * 98304 - 5, 2 * 98304 - 7), 256
+    groups = [host.corr.GroupDesc(n, 3, 16, 2) for n in ns]
+    x = [np.zeros((T, n), np.float32) for n in ns]
+
+    def check(c):
+        q = c.n_pushes() // T
+        for n, subsets in zip(ns, (3, 2)):
+            out = (ctypes.c_int64 * 4096)()
+            k = host.L.stub_folded(ctypes.c_int64(n), out, 4096)
+            got = list(out[:k])
+            for j in range(subsets):
+                assert [v // 1000000 for v in got if v % 1000000 == j] == list(range(1, q + 1)), (n, j)
+            assert len(got) == subsets * q
+
+    with host.context(groups) as c:
+        def steps(n):
+            rows = (ctypes.c_void_p * 2)(*[a.ctypes.data for a in x])
+            host.L.corr_push_steps(c._h, n, rows, (ctypes.c_int64 * 2)(*[a.strides[0] for a in x]))
+
+        def again(f, n):
+            """f to n more pushes, repeated for what is missing."""
+            want, tries = c.n_pushes() + n, 0
+            while c.n_pushes() < want:
+                f(want - c.n_pushes())
+                tries += 1
+                assert tries < 4
+
+        def push(n):
+            for _ in range(n):
+                try:
+                    _push(c, x, 0)
+                except host.corr.CorrError:
+                    return
+
+        host.fail("fold", after)
+        again(push, T + 1)
+        again(steps, 100)
+        again(push, T - 101)       # up to a block's end
+        try:
+            c.finalize(0)
+        except host.corr.CorrError:
+            pass
+        again(steps, 1)
+        again(steps, 120)
+        again(push, 3)
+        again(steps, 200)
+        for i in range(2):
+            try:
+                c.finalize(i)
+            except host.corr.CorrError:
+                c.finalize(i)
+        check(c)
+
+
+@pytest.mark.parametrize("others", [False, True])
+@pytest.mark.parametrize("name,after", [("history_fold", 0), ("history_fold", 1), ("history_fold", 2), ("history_fold", 3),
+                                        ("push_batched", 300), ("push_batched", 700)])
+def test_refused_fold_of_a_history(host, others, name, after):
+    """A whole-block fold straight from the history (or a push of the group
+    beside it) refused: the call made again from where the count stands folds
+    every block of both block-deferred groups once and pushes the others once."""
+    n, T, steps = (300, 700), 256, 900
+    x = [np.zeros((steps, k), np.float32) for k in n] + ([np.zeros((steps, 5), np.float32)] if others else [])
+    for a in x:
+        a[:, 0] = np.arange(1, steps + 1)
+    groups = [host.corr.GroupDesc(k, 3, 16, 2) for k in n] + ([host.corr.GroupDesc(5, 3, 8, 2)] if others else [])
+    with host.context(groups) as c:
+        for s in range(3):
+            _push(c, x, s)
+        host.fail(name, after - 3 if name == "push_batched" else after)
+        failed = 0
+        while c.n_pushes() < steps:
+            at = c.n_pushes()
+            rows = (ctypes.c_void_p * len(x))(*[a[at:].ctypes.data for a in x])
+            if host.L.corr_push_steps(c._h, steps - at, rows, (ctypes.c_int64 * len(x))(*[a.strides[0] for a in x])):
+                failed += 1
+                assert failed < 3
+        for i in range(len(x)):
+            c.finalize(i)
+        out = (ctypes.c_int64 * 4096)()
+        for k in n:
+            got = out[:host.L.stub_folded(ctypes.c_int64(k), out, 4096)]
+            assert [v // 1000000 for v in got] == list(range(1, steps // T + 1)), (k, failed)
+        if others:
+            _every_push_once(host, 5, steps)
+
+
+def test_refused_push_between_scheduled_folds(host):
+    """A replay that stops between the pushes at which two subsets fold: the
+    subset whose push was counted folds at the next call."""
+    n, T = 2 * 98304, 256
+    x = [np.zeros((600, n), np.float32), np.zeros((600, 5), np.float32)]
+    x[1][:, 0] = np.arange(1, 601)
+    groups = [host.corr.GroupDesc(n, 3, 16, 2), host.corr.GroupDesc(5, 3, 8, 2)]
+    with host.context(groups) as c:
+        for s in range(T):
+            _push(c, x, s)
+        host.fail("push_batched", 2)
+        for _ in range(2):
+            at = c.n_pushes()
+            rows = (ctypes.c_void_p * 2)(*[a[at:].ctypes.data for a in x])
+            rc = host.L.corr_push_steps(c._h, T + 10 - at, rows, (ctypes.c_int64 * 2)(*[a.strides[0] for a in x]))
+            assert (rc == 0) == (at > T) and c.n_pushes() == (T + 10 if at > T else T + 2)
+        for s in range(T + 10, 600):
+            _push(c, x, s)
+        c.finalize(0)
+        out = (ctypes.c_int64 * 64)()
+        got = out[:host.L.stub_folded(ctypes.c_int64(n), out, 64)]
+        for j in range(2):
+            assert [v // 1000000 for v in got if v % 1000000 == j] == [1, 2], j
+        _every_push_once(host, 5, 600)
